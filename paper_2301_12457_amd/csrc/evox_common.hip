@@ -21,6 +21,26 @@
 
 namespace evox {
 
+// Compiled in evox_fn.hip, once per function: without these declarations this
+// unit would hold a second copy of every one of those kernels.
+#define EVOX_EXTERN_FN(F)                                                                                          \
+    extern template hipError_t launch_pso_t<F>(Layout, int, const PsoArgs &, int, hipStream_t);                    \
+    extern template hipError_t launch_pso_small_t<F>(Layout, const PsoArgs &, int64_t, float *, DevBest *,         \
+                                                     hipStream_t);                                                 \
+    extern template hipError_t launch_eval_t<F>(Layout, bool, const EvalArgs &, int, hipStream_t);                 \
+    extern template hipError_t launch_cso_t<F>(Layout, const CsoArgs &, int, hipStream_t);                         \
+    extern template hipError_t launch_de_t<F>(Layout, const DeArgs &, int, hipStream_t);                           \
+    extern template hipError_t launch_es_eval_t<F>(Layout, const EsArgs &, int, hipStream_t);                      \
+    extern template hipError_t launch_mae_eval_t<F>(Layout, const MaeEvalArgs &, int, hipStream_t);                \
+    extern template int occupancy_cso_t<F>(Layout, bool);
+EVOX_EXTERN_FN(FN_SPHERE)
+EVOX_EXTERN_FN(FN_ACKLEY)
+EVOX_EXTERN_FN(FN_RASTRIGIN)
+EVOX_EXTERN_FN(FN_GRIEWANK)
+EVOX_EXTERN_FN(FN_ROSENBROCK)
+EVOX_EXTERN_FN(FN_SCHWEFEL)
+#undef EVOX_EXTERN_FN
+
 // ---------------------------------------------------------------------------
 // Initialisation (Algorithm.setup): x ~ U[lb, ub), v ~ U[v_lo, v_hi) or 0,
 // p = x; padding columns zero.  One thread per float4 chunk.
