@@ -56,6 +56,24 @@ int cso_grid_cap(int64_t ldx)
     return (int)cap;
 }
 
+// Individuals per range of the CSO generation kernels: kCsoSweep, halved while
+// that gives at most kCsoRanges ranges and a range still fills the block's row
+// slots (rpb).  A block moves the losers of its range rpb at a time, so a
+// small swarm in few long ranges is a serial chain in a few blocks (1001 x
+// 1000, one row per block: 8 ranges of 128 took 101 us per generation, 501 of
+// 2 take 10.6); each range also adds a row of column sums to the swarm mean
+// (1001 ranges of 1: 10.6 us, but the mean 12 instead of 5).  Measured per
+// generation with at most half / this / twice as many ranges: 1001 x 1000
+// 17.3 / 17.6 / 22.3 us, 10,000 x 100 16.7 / 15.5 / 15.9, 4000 x 500 19.9 /
+// 20.3 / 24.3 (108.6, 27.6 and 75.1 with ranges of 128).
+constexpr int64_t kCsoRanges = 640;
+int cso_sweep(int64_t N, int rpb)
+{
+    int r = kCsoSweep;
+    while (r > rpb && (N + r / 2 - 1) / (r / 2) <= kCsoRanges) r /= 2;
+    return r;
+}
+
 int grid_for(int64_t groups, int G, int64_t cap)
 {
     const int64_t rpb = block_for(G) / G;
@@ -73,7 +91,7 @@ T *at_off(void *base, size_t off)
 
 struct Plan {
     Layout L{0, 0, 0};
-    int grid = 0, cso_grid = 0, colsum_grid = 0, bits = 0;
+    int grid = 0, cso_grid = 0, cso_sweep = 0, colsum_grid = 0, bits = 0;
     size_t best = 0, slots = 0;
     size_t hist = 0, offs = 0, cursor = 0, tkv = 0, perm = 0, xsum = 0, s1 = 0, ticket = 0;
     int64_t xsum_rows = 0;
@@ -201,9 +219,6 @@ int make_plan(const evox_params *P, Plan *pl)
     p.slots = take(sizeof(SelSlots));
     if (P->algo == EVOX_CSO) {
         const int cap = cso_grid_cap(P->ldx);
-        // both versions sweep ranges of individuals
-        int64_t ranges = (P->N + kCsoSweep - 1) / kCsoSweep;
-        p.cso_grid = (int)(ranges > cap ? cap : ranges);
         p.colsum_grid = grid_for(P->N, p.L.G, cap);
         p.bits = perm_bits(P->N);
         // permutations and their mate arrays sorted kPermBatch generations
@@ -560,12 +575,16 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
     if (P.algo == EVOX_CSO) {
         // persistent grid for the pair kernel: every block resident at once
         int dev = 0, cus = 0;
+        int64_t resident = 256;
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
             const int occ = occupancy_cso(P.fn_id, pl.L, P.cso_local != 0);
-            const int64_t resident = (int64_t)cus * (occ > 0 ? occ : 1);
-            if (resident < s->pl.cso_grid) s->pl.cso_grid = (int)resident;
+            resident = (int64_t)cus * (occ > 0 ? occ : 1);
         }
+        s->pl.cso_sweep = cso_sweep(P.N, block_for(pl.L.G) / pl.L.G);
+        const int64_t ranges = (P.N + s->pl.cso_sweep - 1) / s->pl.cso_sweep;
+        s->pl.cso_grid = (int)(ranges < resident ? ranges : resident);
+        if (s->pl.cso_grid > pl.xsum_rows) s->pl.cso_grid = (int)pl.xsum_rows;
     }
 
     hipError_t e;
@@ -871,7 +890,7 @@ int evox_cso_step(evox_state *s, int64_t n_gens)
         float *dst = local ? (cur == s->B.x ? alt : s->B.x) : s->B.x;
         float *fnext = fcur == s->B.fit ? s->cfit2 : s->B.fit;
         CsoArgs ca{dst, s->B.v, fnext, fcur, s->B.xbar, s->perm + slice, s->mate + slice,
-                   P.N, P.D, P.ldx, P.phi, P.lb, P.ub, P.clamp_x != 0, s->k0, s->k1, (uint32_t)t, s->slots,
+                   P.N, P.D, P.ldx, pl.cso_sweep, P.phi, P.lb, P.ub, P.clamp_x != 0, s->k0, s->k1, (uint32_t)t, s->slots,
                    s->xsum, cur};
         e = timed(s, [&] { return launch_cso(P.fn_id, pl.L, ca, pl.cso_grid, s->stream); });
         if (e != hipSuccess) return hip_fail(e, "cso generation");

@@ -635,6 +635,18 @@ hipError_t launch_pair_move(int G, float *x, float *v, int64_t N, int64_t D, int
     }
 }
 
+// Handing data to another block of the same launch: the stores are written
+// through to memory (agent-scope atomic stores) and waited for before the
+// block signals, and the reader's agent-scope atomic loads go past its own
+// caches.  A release fence in its place writes back everything that is dirty
+// in the L2 (k_cso_mean over 1001 partial rows of 1000 columns: 15.8 us with
+// one fence per block).
+__device__ __forceinline__ void store_through(double *p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Block (0, 0) also finishes the selection (slots -> best) when asked.
 // xbar = (sum of the per-block partial rows) / N, rounded once, in two
 // stages.  Block (tile, rg) of 64 columns x 4 lanes: lane l sums partial rows
@@ -696,15 +708,14 @@ __global__ __launch_bounds__(256) void k_cso_mean(MeanArgs m)
     if (j < m.D) s = strided_sum(m.xsum + j, rg + (int64_t)m.stages * lane, 4 * (int64_t)m.stages, m.nparts, m.ldx);
     part[lane][col] = s;
     __syncthreads();
-    if (lane == 0) {  // wave 0 writes this block's stage sums and releases them
-        if (j < m.D) m.s1[rg * m.ldx + j] = ((part[0][col] + part[1][col]) + part[2][col]) + part[3][col];
-        __threadfence();
+    if (lane == 0) {  // wave 0 writes this block's stage sums through to memory
+        if (j < m.D) store_through(m.s1 + rg * m.ldx + j, ((part[0][col] + part[1][col]) + part[2][col]) + part[3][col]);
+        wait_stores();
     }
     __syncthreads();
     if (threadIdx.x == 0) last = atomicAdd(&m.ticket[tile], 1u) == (uint32_t)(m.stages - 1);
     __syncthreads();
     if (last) {
-        __threadfence();
         double t = 0.0;
         if (j < m.D) t = strided_sum(m.s1 + j, lane, 4, m.stages, m.ldx);
         part[lane][col] = t;

@@ -445,7 +445,7 @@ struct ColAcc {
 
 // ---------------------------------------------------------------------------
 // The swarm-mean generation, swept in individual order.  A block takes
-// ranges of kCsoSweep consecutive individuals: every individual of the range
+// ranges of a.sweep consecutive individuals: every individual of the range
 // reads its mate entry and both fitness values (before the generation) and
 // decides whether it lost its pair; winners (and the odd one out) copy their
 // fitness to the output buffer, losers are listed in LDS in index order (a
@@ -461,20 +461,21 @@ struct ColAcc {
 template <int FN, int G, int MAXIT>
 __device__ __forceinline__ void cso_sweep_body(const CsoArgs &a)
 {
-    constexpr int B = block_for(G), RPB = B / G, NW = B / 64, R = kCsoSweep;
-    static_assert(R <= B, "one individual per thread in the decision phase");
+    constexpr int B = block_for(G), RPB = B / G, NW = B / 64;
+    static_assert(kCsoSweep <= B, "one individual per thread in the decision phase");
     __shared__ float nbr[(FN == FN_ROSENBROCK && G > 64) ? B * MAXIT : 1];
     __shared__ float red[2 * (B / 64)];
     __shared__ uint64_t sk[B / 64];
     __shared__ uint32_t sc[B / 64];
     __shared__ double acc_lds[RPB > 1 ? 4 * MAXIT * B : 1];
-    __shared__ int32_t lst_l[R], lst_w[R];  // listed individual, its winner (-1: the odd one out)
+    __shared__ int32_t lst_l[kCsoSweep], lst_w[kCsoSweep];  // listed individual, its winner (-1: the odd one out)
     __shared__ int32_t wcnt[NW];
 
     const int tid = threadIdx.x, g = tid % G, slot = tid / G, lane = tid & 63, wave = tid >> 6;
     const int64_t C4 = (a.D + 3) >> 2;
     uint64_t best = kNoKey;
     uint32_t none = 0;
+    const int R = a.sweep;
     ColAcc<G, MAXIT> acc(acc_lds);
 
     for (int64_t base = (int64_t)blockIdx.x * R; base < a.N; base += (int64_t)gridDim.x * R) {
@@ -583,7 +584,7 @@ __device__ __forceinline__ void cso_sweep_body(const CsoArgs &a)
 // ---------------------------------------------------------------------------
 // The neighbourhood version's generation, swept in individual order like
 // the swarm version: the old positions are read from xs and every row of the
-// next population buffer x is written.  Per range of kCsoSweep individuals
+// next population buffer x is written.  Per range of a.sweep individuals
 // each one decides from its mate entry and both fitness values (before the
 // generation) whether it lost; the others (winners and the odd one out) are
 // listed first and copied, x_i = xs_i, their fitness carried over; then the
@@ -595,21 +596,22 @@ __device__ __forceinline__ void cso_sweep_body(const CsoArgs &a)
 template <int FN, int G, int MAXIT>
 __device__ __forceinline__ void cso_local_body(const CsoArgs &a)
 {
-    constexpr int B = block_for(G), RPB = B / G, NW = B / 64, R = kCsoSweep;
-    static_assert(R <= B, "one individual per thread in the decision phase");
+    constexpr int B = block_for(G), RPB = B / G, NW = B / 64;
+    static_assert(kCsoSweep <= B, "one individual per thread in the decision phase");
     __shared__ float nbr[(FN == FN_ROSENBROCK && G > 64) ? B * MAXIT : 1];
     __shared__ float red[2 * (B / 64)];
     __shared__ uint64_t sk[B / 64];
     __shared__ uint32_t sc[B / 64];
     __shared__ double acc_lds[RPB > 1 ? 4 * MAXIT * B : 1];
-    __shared__ int32_t lst_c[R];            // copied individuals (winners, the odd one out)
-    __shared__ int32_t lst_l[R], lst_w[R];  // losers and their winners
+    __shared__ int32_t lst_c[kCsoSweep];            // copied individuals (winners, the odd one out)
+    __shared__ int32_t lst_l[kCsoSweep], lst_w[kCsoSweep];  // losers and their winners
     __shared__ int32_t ccnt[NW], lcnt[NW];
 
     const int tid = threadIdx.x, g = tid % G, slot = tid / G, lane = tid & 63, wave = tid >> 6;
     const int64_t C4 = (a.D + 3) >> 2;
     uint64_t best = kNoKey;
     uint32_t none = 0;
+    const int R = a.sweep;
     ColAcc<G, MAXIT> acc(acc_lds);
 
     for (int64_t base = (int64_t)blockIdx.x * R; base < a.N; base += (int64_t)gridDim.x * R) {

@@ -205,7 +205,7 @@ struct InitArgs {
 // the individual left over when N is odd.
 constexpr uint32_t kMateFirst = 0x80000000u;
 constexpr uint32_t kUnpaired = 0xFFFFFFFFu;
-constexpr int kCsoSweep = 128;  // individuals per range of the swarm-mean generation kernel
+constexpr int kCsoSweep = 128;  // individuals per range of the generation kernels at most
 
 struct CsoArgs {
     float *x, *v;
@@ -215,6 +215,7 @@ struct CsoArgs {
     const uint32_t *perm;  // this generation's permutation (not read by the generation kernels)
     const uint32_t *mate;  // this generation's mate array
     int64_t N, D, ldx;
+    int32_t sweep;         // individuals per range, 1 .. kCsoSweep
     float phi, lb, ub;
     int32_t xclamp;
     uint32_t k0, k1, t;

@@ -209,3 +209,25 @@ def test_neighbourhood_flag_only_for_cso(evox_gpu):
         ev.Swarm(ev.make_params(ev.PSO, 0, 10, 5, -1.0, 1.0, cso_local=1))
     with pytest.raises(ev.EvoxError):
         ev.Swarm(ev.make_params(ev.CSO, 0, 10, 5, -1.0, 1.0, cso_local=2))
+
+
+# swarm sizes on both sides of each halving of the ranges that a block sweeps:
+# 640 ranges of one round of rows (G = 4, 32 and 256 lanes per row: 64, 8 and
+# 1 rows per round) and the next longer ranges, and rows of 1024 lanes
+RANGE_CASES = [(0, 40_960, 3), (0, 40_961, 3), (3, 5_120, 100), (3, 5_121, 100), (4, 640, 1000), (4, 641, 1000),
+               (2, 1_283, 997), (4, 3, 4_100)]
+
+
+@pytest.mark.parametrize("local", [0, 1])
+@pytest.mark.parametrize("fn,N,D", RANGE_CASES)
+def test_range_lengths_match_oracle(evox_gpu, ref, fn, N, D, local):
+    lb, ub = {0: (-32.0, 32.0), 2: (-5.12, 5.12), 3: (-600.0, 600.0), 4: (-2.0, 2.0)}[fn]
+    print(f"cso ranges fn={fn} N={N} D={D} local={local}", flush=True)
+    g, r = pair(evox_gpu, ref, fn, N, D, 17, lb, ub, cso_local=local)
+    for t in range(2):
+        if local:
+            g.step(1)
+            r.step(1)
+        else:
+            cso_lockstep(ref, g, r, f"generation {t}")
+        compare(g, r, fn, f"generation {t}")
