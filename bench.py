@@ -63,11 +63,13 @@ def traffic_from_profile(name):
 
 
 def pso_bytes_per_generation(w, evaluations, improved_rows):
-    # read x, v, pbest and write x, v (20 B per element); read pfit (4 B per
-    # row); write pbest row and pfit of each improved row (the kernels' count
-    # over `evaluations` generations)
+    # read and write x and v (16 B per element); read the pbest rows that did
+    # not improve in the generation before (the others are in x); per row
+    # read pfit and the mark of its pbest, write the fitness.  The pbest rows
+    # written when they stop improving are not counted (the kernels count
+    # improved rows only), so the figure is a lower bound.
     imp = improved_rows / max(evaluations, 1)
-    return 20.0 * w.N * w.D + 4.0 * w.N + (4.0 * w.D + 4.0) * imp
+    return 16.0 * w.N * w.D + 4.0 * w.D * (w.N - imp) + 12.0 * w.N
 
 
 def de_bytes_per_launch(w):
@@ -288,10 +290,10 @@ def cso_data_floor(torch, evox, w, ldx, reps=5):
 
 
 def pso_data_floor(torch, evox, w, ldx, reps=5):
-    """The data-movement floor of the PSO generation on this GPU: its 20 B per
-    element (read x, v, pbest; write x, v) streamed alone by evox_pso_stream
-    over arrays of the swarm's N x ldx floats, timed like the generation
-    kernel.  Returns its average launch duration and the algorithmic bytes
+    """A stream of the shape of a PSO generation on this GPU: 20 B per element
+    (read x, v, pbest; write x, v) and nothing else, by evox_pso_stream over
+    arrays of the swarm's N x ldx floats, timed like the generation kernel
+    (which moves 16 B and the pbest rows that change hands).  Returns its average launch duration and the algorithmic bytes
     per launch (20 B per element of the N x D swarm)."""
     n = w.N * ldx
     x = torch.zeros(n, dtype=torch.float32, device="cuda")
@@ -492,10 +494,9 @@ def measure(torch, evox, w, steps, warmup, ldx):
                         "avg_launch_us": round(avg_ms * 1e3, 2), "launches": launches,
                         "algorithmic_bytes_per_launch": bytes_per}
             if w.algo == "pso":
-                # the 20 B per element floor alone (read x, v, pbest; write
-                # x, v), without the rows whose personal best improved
-                floor_bytes = 20.0 * w.N * w.D
-                roofline["frac_floor_20B"] = round(floor_bytes / (avg_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4)
+                # the 16 B per element alone that every row moves (x and v)
+                floor_bytes = 16.0 * w.N * w.D
+                roofline["frac_floor_16B"] = round(floor_bytes / (avg_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4)
                 roofline["improved_rows_per_generation"] = round(improved / (steps * w.gens), 1)
                 if launches == steps * w.gens:
                     # the one-block kernel: one launch per step, the figures

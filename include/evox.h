@@ -463,9 +463,9 @@ int evox_copy(const float *src, float *dst, int64_t n, void *hip_stream);
 int evox_pair_move(float *x, float *v, int64_t N, int64_t D, int64_t ldx, const int32_t *winner_of,
                    void *hip_stream);
 
-/* Diagnostic, the data-movement floor of the PSO generation: its 20 bytes
- * per element (read x, v, pbest; write x, v; Sec. IV-B, Eq. (1)-(3) as
- * evox_pso_step runs them) streamed with nothing else: for every q < n,
+/* Diagnostic, a stream of the shape of a PSO generation (Sec. IV-B, Eq.
+ * (1)-(3)): 20 bytes per element (read x, v, pbest; write x, v; evox_pso_step
+ * itself reads and writes pbest rows only where they change) and nothing else: for every q < n,
  * v[q] = v[q] + (p[q] - x[q]), then x[q] = x[q] + v[q] (device x, v, p of n
  * floats each, 16-byte aligned, n a multiple of 4; pass N * ldx for a swarm).
  * One 16-byte element per thread with nontemporal loads and stores, the shape

@@ -96,6 +96,7 @@ struct Plan {
     size_t hist = 0, offs = 0, cursor = 0, tkv = 0, perm = 0, xsum = 0, s1 = 0, ticket = 0;
     int64_t xsum_rows = 0;
     int perm_batch = 0;
+    size_t lag = 0;           // PSO: marks of the rows whose personal best is the x row
     size_t x2 = 0, fit2 = 0;  // DE: the other population buffer and its fitness
     size_t xalt = 0;          // CSO neighbourhood version: the other population buffer
     size_t mate = 0, cfit2 = 0;  // CSO: mate arrays, the other fitness buffer
@@ -217,6 +218,7 @@ int make_plan(const evox_params *P, Plan *pl)
     };
     p.best = take(sizeof(DevBest));
     p.slots = take(sizeof(SelSlots));
+    if (P->algo == EVOX_PSO) p.lag = take(sizeof(uint32_t) * (size_t)P->N);
     if (P->algo == EVOX_CSO) {
         const int cap = cso_grid_cap(P->ldx);
         p.colsum_grid = grid_for(P->N, p.L.G, cap);
@@ -311,6 +313,7 @@ struct evox_state {
     uint2 *tkv;
     int64_t perm_t0;  // first generation of the stored permutation batch (-1: none)
     double *xsum, *s1;
+    uint32_t *lag;     // PSO: marks of the rows whose personal best is the x row
     float *x2, *fit2;  // DE: the other population buffer
     uint32_t *esrank;  // ES: sample ranks
     double *espart;    // ES: gradient partial sums
@@ -370,6 +373,7 @@ PsoArgs pso_args(evox_state *s)
     a.p = s->B.pbest;
     a.pf = s->B.pfit;
     a.fit = s->B.fit;
+    a.lag = s->lag;
     a.gbest = s->B.gbest;
     a.N = P.N;
     a.D = P.D;
@@ -479,6 +483,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
     s->xsum = s->s1 = nullptr;
     s->perm_t0 = -1;
     s->ticket = nullptr;
+    s->lag = P.algo == EVOX_PSO ? at<uint32_t>(b->scratch, pl.lag) : nullptr;
     s->x2 = s->fit2 = nullptr;
     s->esrank = nullptr;
     s->espart = nullptr;
@@ -654,7 +659,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         if ((e = launch_fill(s->x2, P.N * P.ldx, 0.0f, s->stream)) != hipSuccess ||
             (e = best_init(s, std::numeric_limits<float>::infinity(), 0)) != hipSuccess ||
             (e = launch_eval(P.fn_id, pl.L, true, ea, pl.grid, s->stream)) != hipSuccess ||
-            (e = launch_select(s->slots, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess) {
+            (e = launch_select(s->slots, nullptr, nullptr, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess) {
             delete s;
             return hip_fail(e, "init");
         }
@@ -749,7 +754,7 @@ int evox_eval_argmin(int fn_id, const float *X, int64_t N, int64_t D, int64_t ld
     if (e != hipSuccess) return hip_fail(e, "select init");
     rc = eval_common(fn_id, X, N, D, ldx, out, slots, st);
     if (rc != EVOX_OK) return rc;
-    e = launch_select(slots, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st);
+    e = launch_select(slots, nullptr, nullptr, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st);
     if (e != hipSuccess) return hip_fail(e, "select");
     return EVOX_OK;
 }
@@ -818,7 +823,7 @@ int evox_eval_argmin_noalloc(int fn_id, const float *X, int64_t N, int64_t D, in
     if ((e = launch_slots_init(slots, st)) != hipSuccess) return hip_fail(e, "select init");
     rc = eval_common(fn_id, X, N, D, ldx, out, slots, st);
     if (rc != EVOX_OK) return rc;
-    if ((e = launch_select(slots, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st)) != hipSuccess)
+    if ((e = launch_select(slots, nullptr, nullptr, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st)) != hipSuccess)
         return hip_fail(e, "select");
     return EVOX_OK;
 }
@@ -843,20 +848,20 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
         return EVOX_OK;
     }
     // generation t: evaluate x_t, personal and global bests
-    if ((e = launch_pso(fn, pl.L, PSO_EVAL, a, pl.grid, s->stream)) != hipSuccess) return hip_fail(e, "pso eval");
-    if ((e = launch_select(s->slots, s->B.pbest, s->P.ldx, s->B.gbest, s->best, nullptr, nullptr,
+    if ((e = launch_pso(fn, pl.L, PSO_EVAL, a, s->stream)) != hipSuccess) return hip_fail(e, "pso eval");
+    if ((e = launch_select(s->slots, s->B.pbest, s->B.x, s->lag, s->P.ldx, s->B.gbest, s->best, nullptr, nullptr,
                            s->stream)) != hipSuccess)
         return hip_fail(e, "select");
     for (int64_t k = 1; k < n_gens; ++k) {
         a.t = (uint32_t)(s->t + k - 1);  // move of generation t+k-1, evaluation of t+k
-        e = timed(s, [&] { return launch_pso(fn, pl.L, PSO_FUSED, a, pl.grid, s->stream); });
+        e = timed(s, [&] { return launch_pso(fn, pl.L, PSO_FUSED, a, s->stream); });
         if (e != hipSuccess) return hip_fail(e, "pso generation");
-        if ((e = launch_select(s->slots, s->B.pbest, s->P.ldx, s->B.gbest, s->best, nullptr, nullptr,
+        if ((e = launch_select(s->slots, s->B.pbest, s->B.x, s->lag, s->P.ldx, s->B.gbest, s->best, nullptr, nullptr,
                                s->stream)) != hipSuccess)
             return hip_fail(e, "select");
     }
     a.t = (uint32_t)(s->t + n_gens - 1);
-    if ((e = launch_pso(fn, pl.L, PSO_MOVE, a, pl.grid, s->stream)) != hipSuccess) return hip_fail(e, "pso move");
+    if ((e = launch_pso(fn, pl.L, PSO_MOVE, a, s->stream)) != hipSuccess) return hip_fail(e, "pso move");
     s->t += n_gens;
     return EVOX_OK;
 }
@@ -927,7 +932,7 @@ int evox_de_step(evox_state *s, int64_t n_gens)
         e = timed(s, [&] { return launch_de(P.fn_id, pl.L, a, pl.grid, s->stream); });
         if (e != hipSuccess) return hip_fail(e, "de generation");
     }
-    if ((e = launch_select(s->slots, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
+    if ((e = launch_select(s->slots, nullptr, nullptr, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
         return hip_fail(e, "select");
     if (n_gens & 1) {  // the population ended in the other buffer: bring it home
         if ((e = launch_stream_copy(s->x2, s->B.x, P.N * P.ldx, s->stream)) != hipSuccess ||
@@ -965,7 +970,7 @@ int es_generations(evox_state *s, int64_t n_gens, bool pgpe)
                       P.pgpe_sigma_lr, P.pgpe_max_change, s->k0, s->k1, t, stream};
         if ((e = launch_es_grad(ga, s->stream)) != hipSuccess) return hip_fail(e, "gradient");
     }
-    if ((e = launch_select(s->slots, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
+    if ((e = launch_select(s->slots, nullptr, nullptr, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
         return hip_fail(e, "select");
     s->t += n_gens;
     return EVOX_OK;
@@ -1029,7 +1034,7 @@ int mae_generations(evox_state *s, int64_t n_gens)
         if ((e = launch_mae_rank(m, s->B.mat, s->mae_beta, s->stream)) != hipSuccess)
             return hip_fail(e, "matrix update");
     }
-    if ((e = launch_select(s->slots, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
+    if ((e = launch_select(s->slots, nullptr, nullptr, nullptr, 0, nullptr, s->best, nullptr, nullptr, s->stream)) != hipSuccess)
         return hip_fail(e, "select");
     s->t += n_gens;
     return EVOX_OK;

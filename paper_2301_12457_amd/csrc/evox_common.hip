@@ -93,11 +93,12 @@ hipError_t launch_init(const InitArgs &a, hipStream_t s)
 // ---------------------------------------------------------------------------
 // Second pass of the selection: one block reduces the kSlots keys (and the
 // improved-row counts), resets them for the next launch, stores the result,
-// and copies the selected row (ldx floats) to row_out.
+// and copies the selected row (ldx floats; from rows_lag where the mark says
+// so) to row_out.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_select(SelSlots *sl, const float *rows, int64_t ldx,
-                                                 float *row_out, DevBest *best, float *bf_out,
-                                                 int64_t *bi_out)
+__global__ __launch_bounds__(1024) void k_select(SelSlots *sl, const float *rows, const float *rows_lag,
+                                                 const uint32_t *lag, int64_t ldx, float *row_out,
+                                                 DevBest *best, float *bf_out, int64_t *bi_out)
 {
     __shared__ uint64_t sk[16];
     __shared__ uint32_t sc[16];
@@ -126,15 +127,15 @@ __global__ __launch_bounds__(1024) void k_select(SelSlots *sl, const float *rows
     }
     __syncthreads();
     if (row_out) {
-        const float *src = rows + sel * ldx;
+        const float *src = (lag && lag[sel] ? rows_lag : rows) + sel * ldx;
         for (int64_t j = threadIdx.x; j < ldx; j += blockDim.x) row_out[j] = src[j];
     }
 }
 
-hipError_t launch_select(SelSlots *slots, const float *rows, int64_t ldx, float *row_out,
-                         DevBest *best, float *best_f_out, int64_t *best_i_out, hipStream_t s)
+hipError_t launch_select(SelSlots *slots, const float *rows, const float *rows_lag, const uint32_t *lag, int64_t ldx,
+                         float *row_out, DevBest *best, float *best_f_out, int64_t *best_i_out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, s, slots, rows, ldx, row_out, best,
+    hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, s, slots, rows, rows_lag, lag, ldx, row_out, best,
                        best_f_out, best_i_out);
     return hipGetLastError();
 }
@@ -761,11 +762,23 @@ hipError_t launch_colsum(Layout L, const float *x, int64_t N, int64_t D, int64_t
     default: return hipErrorInvalidValue;                                                         \
     }
 
-hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &a, int grid, hipStream_t s)
+static hipError_t launch_pso_rows(int fn, Layout L, int mode, const PsoArgs &a, int grid, hipStream_t s)
 {
     if (mode == PSO_MOVE) fn = FN_SPHERE;  // the move does not evaluate
 #define EVOX_CALL_PSO(F) launch_pso_t<F>(L, mode, a, grid, s)
     EVOX_FN_SWITCH(EVOX_CALL_PSO)
+}
+
+hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &args, hipStream_t s)
+{
+    PsoArgs a = args;
+    const int64_t rpb = block_for(L.G) / L.G;
+    for (a.row0 = 0; a.row0 < a.N; a.row0 += kMaxGrid * rpb) {
+        const int64_t groups = (a.N - a.row0 + rpb - 1) / rpb;
+        const hipError_t e = launch_pso_rows(fn, L, mode, a, (int)(groups < kMaxGrid ? groups : kMaxGrid), s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_pso_small(int fn, Layout L, const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best,

@@ -11,8 +11,16 @@
 //                 block argmin partials, all from one read of x, v, pbest
 //   k_pso<MOVE>   the final move of a call (nothing to evaluate after it)
 // so an n-generation call is EVAL, select, (n-1) x (FUSED, select), MOVE:
-// one HBM pass of 20 B per element per generation (read x, v, p; write x, v)
-// plus 4 B per element of rows whose personal best improved.
+// one HBM pass per generation that reads and writes x and v, 16 B per
+// element, and pbest only where it changes hands: an improved row is not
+// copied to pbest but marked (lag), since the personal best is then the row
+// that x holds; the next move reads it from x, and it is written to pbest, from
+// the registers of that move, only if the row does not improve again.  A
+// marked row costs no pbest read, and a row that keeps improving no pbest
+// write either.  MOVE writes the marked rows, so pbest is whole at the end of
+// every call.  Rastrigin 1e5 x 1e3, a call of 8 generations: 3300 us with every
+// improved row copied, 3034 with the marks, 2540 with the row's loads in flight
+// together as well (k_pso).
 //
 // CSO (the competitive swarm optimizer of Table II).  k_cso / k_cso5 sweep
 // the individuals in index order: each decides from its mate entry and the
@@ -36,6 +44,16 @@ namespace evox {
 // Philox stream 2 (counters 2c and 2c + 1), vn = fma(c2 r2, g - x, fma(c1 r1,
 // p - x, w v)), optional clamps, x + vn; elements past D give zeros.
 // ---------------------------------------------------------------------------
+// The row of a lane group of at least a wave is the same in all its lanes:
+// known to the compiler, its addresses and the words of Philox that depend on
+// it alone are scalar.
+template <int G>
+__device__ __forceinline__ int64_t uniform_row(int64_t row)
+{
+    if constexpr (G >= 64) return __builtin_amdgcn_readfirstlane((int)row);
+    return row;
+}
+
 __device__ __forceinline__ void pso_move4(const PsoArgs &a, int64_t row, int64_t c, float4 xv, float4 vv,
                                           float4 pv, float4 gv, float4 &xn, float4 &vn)
 {
@@ -61,85 +79,125 @@ __device__ __forceinline__ void pso_move4(const PsoArgs &a, int64_t row, int64_t
 
 // ---------------------------------------------------------------------------
 // The PSO generation kernel (modes above).  One group of block_for(G) / G
-// rows per block (grid-stride only beyond kMaxGrid blocks); the loop bound is
-// uniform over the block, so the barriers inside row_fitness are reached by
-// every thread.  Each block folds its best (pfit, row) into a selection slot.
+// rows per block, the rows from a.row0 on (a swarm of more than kMaxGrid such
+// groups takes several launches: a loop over row groups inside the kernel
+// keeps what does not depend on the row in registers, 109 of them and 4 waves
+// per SIMD instead of 59 and 8).  Loads are unconditional -- lanes past the row
+// read its last chunk, rows past the swarm its last row, and both are
+// discarded -- and NT is a template parameter, so that no branch stands between
+// a row's loads and all of them are in flight together.  Each block folds its
+// best (pfit, row) into a selection slot.
 // ---------------------------------------------------------------------------
-template <int FN, int G, int MAXIT, int MODE>
+template <bool NT>
+__device__ __forceinline__ float4 ld_row_t(const float *p)
+{
+    return NT ? ld_stream(p) : *reinterpret_cast<const float4 *>(p);
+}
+template <bool NT>
+__device__ __forceinline__ void st_row_t(float *p, float4 v)
+{
+    if constexpr (NT)
+        st_stream(p, v);
+    else
+        *reinterpret_cast<float4 *>(p) = v;
+}
+
+template <int FN, int G, int MAXIT, int MODE, bool NT>
 __global__ __launch_bounds__(block_for(G)) void k_pso(PsoArgs a)
 {
-    constexpr int B = block_for(G), RPB = B / G;
+    constexpr int B = block_for(G), RPB = B / G, U = 2;  // chunks loaded together
     constexpr bool MOVE = MODE != PSO_EVAL, EVAL = MODE != PSO_MOVE;
+    static_assert(MAXIT % U == 0, "whole pairs of chunks");
     __shared__ float nbr[(FN == FN_ROSENBROCK && G > 64) ? B * MAXIT : 1];
     __shared__ float red[2 * (B / 64)];
     __shared__ uint64_t sk[B / 64];
     __shared__ uint32_t sc[B / 64];
 
     const int tid = threadIdx.x, g = tid % G, slot = tid / G;
-    const int64_t C4 = (a.D + 3) >> 2;
+    const uint32_t C4 = (uint32_t)((a.D + 3) >> 2);
     // chunks written per row: the padding up to the row pitch is rewritten
     // (with zeros) where the lanes cover it, so that rows of a 128-byte-
     // aligned pitch are written as whole cache lines
-    const int64_t CW = a.ldx / 4 < (int64_t)G * MAXIT ? a.ldx / 4 : (int64_t)G * MAXIT;
-    uint64_t best = kNoKey;
-    uint32_t nimp = 0;
+    const uint32_t CW = (uint32_t)(a.ldx / 4 < (int64_t)G * MAXIT ? a.ldx / 4 : (int64_t)G * MAXIT);
+    const int64_t row = a.row0 + (int64_t)blockIdx.x * RPB + slot;
+    const bool active = row < a.N;
+    const int64_t rr = uniform_row<G>(active ? row : a.N - 1);
+    const int64_t ro = rr * a.ldx;
+    float *const xp = a.x + ro, *const vp = a.v + ro, *const pp = a.p + ro;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    for (int64_t rb = (int64_t)blockIdx.x * RPB; rb < a.N; rb += (int64_t)gridDim.x * RPB) {
-        const int64_t row = rb + slot;
-        const bool active = row < a.N;
-        float4 xr[MAXIT];
+    // the row's personal best is its x row (lag), or in pbest.  The mark and
+    // the personal-best fitness are read before the evaluation's block
+    // barriers: when a row spans several waves, lane 0 of its first wave
+    // rewrites both below, and a wave that read them after that would take
+    // the opposite decision for its chunks
+    const bool lag = MOVE && a.lag[rr] != 0;
+    const float pold = EVAL ? a.pf[rr] : 0.0f;
+    float4 xr[MAXIT], xo[MAXIT];
 #pragma unroll
-        for (int it = 0; it < MAXIT; ++it) {
-            const int64_t c = g + (int64_t)G * it;
-            float4 xn = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (active && c < C4) {
-                const int64_t off = row * a.ldx + 4 * c;
-                const float4 xv = ld_row(a.x + off, a.nt);
-                if constexpr (MOVE) {
-                    const float4 vv = ld_row(a.v + off, a.nt);
-                    const float4 pv = ld_row(a.p + off, a.nt);
-                    const float4 gv = *reinterpret_cast<const float4 *>(a.gbest + 4 * c);
-                    float4 vn;
-                    pso_move4(a, row, c, xv, vv, pv, gv, xn, vn);
-                    st_row(a.x + off, xn, a.nt);
-                    st_row(a.v + off, vn, a.nt);
-                } else {
-                    xn = xv;
-                }
-            } else if (MOVE && active && c < CW) {
-                const int64_t off = row * a.ldx + 4 * c;
-                st_row(a.x + off, xn, a.nt);
-                st_row(a.v + off, xn, a.nt);
-            }
-            xr[it] = xn;
+    for (int i0 = 0; i0 < MAXIT; i0 += U) {
+        float4 vv[U], pv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t c = g + G * (i0 + u), cl = 4 * (c < C4 ? c : C4 - 1);
+            xo[i0 + u] = ld_row_t<NT>(xp + cl);
+            if constexpr (MOVE) vv[u] = ld_row_t<NT>(vp + cl);
+            pv[u] = zero;
         }
-        if constexpr (EVAL) {
-            // the personal-best fitness is read before the evaluation's
-            // block barriers: when a row spans several waves, lane 0 of its
-            // first wave rewrites it below, and a wave that read it after
-            // that store would take the opposite decision for its chunks
-            const float pold = active ? a.pf[row] : 0.0f;
-            const float f = row_fitness<FN, G, MAXIT>(xr, g, a.D, nbr, red);
-            if (active) {
-                const bool imp = f < pold;
-                if (imp) {
+        if constexpr (MOVE) {
+            if (!lag) {
 #pragma unroll
-                    for (int it = 0; it < MAXIT; ++it) {
-                        const int64_t c = g + (int64_t)G * it;
-                        if (c < CW) st_row(a.p + row * a.ldx + 4 * c, xr[it], a.nt);
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t c = g + G * (i0 + u), cl = 4 * (c < C4 ? c : C4 - 1);
+                    pv[u] = ld_row_t<NT>(pp + cl);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int it = i0 + u;
+            const uint32_t c = g + G * it;
+            if (c >= C4) xo[it] = zero;
+            if constexpr (MOVE) {
+                float4 xn = zero, vn = zero;
+                if (c < CW) {
+                    if (c < C4) {
+                        const float4 gv = *reinterpret_cast<const float4 *>(a.gbest + 4 * c);
+                        pso_move4(a, rr, c, xo[it], vv[u], lag ? xo[it] : pv[u], gv, xn, vn);
+                    }
+                    if (active) {
+                        st_row_t<NT>(xp + 4 * c, xn);
+                        st_row_t<NT>(vp + 4 * c, vn);
+                        if (!EVAL && lag) st_row_t<NT>(pp + 4 * c, xo[it]);
                     }
                 }
-                if (g == 0) {
-                    if (imp) a.pf[row] = f;
-                    if (a.fit) a.fit[row] = f;
-                    const uint64_t k = sel_key(imp ? f : pold, row);
-                    best = k < best ? k : best;
-                    nimp += imp ? 1u : 0u;
-                }
+                xr[it] = xn;
+            } else {
+                xr[it] = xo[it];
             }
         }
     }
     if constexpr (EVAL) {
+        const float f = row_fitness<FN, G, MAXIT>(xr, g, a.D, nbr, red);
+        uint64_t best = kNoKey;
+        uint32_t nimp = 0;
+        if (active) {
+            const bool imp = f < pold;
+            if (lag && !imp) {
+#pragma unroll
+                for (int it = 0; it < MAXIT; ++it) {
+                    const uint32_t c = g + G * it;
+                    if (c < CW) st_row_t<NT>(pp + 4 * c, xo[it]);
+                }
+            }
+            if (g == 0) {
+                if (imp) a.pf[row] = f;
+                if (!MOVE || imp != lag) a.lag[row] = imp ? 1u : 0u;
+                if (a.fit) a.fit[row] = f;
+                best = sel_key(imp ? f : pold, row);
+                nimp = imp ? 1u : 0u;
+            }
+        }
         block_min_key(best, nimp, sk, sc);
         if (tid == 0) slot_commit(a.slots, best, nimp);
     }
@@ -1089,8 +1147,13 @@ __global__ __launch_bounds__(block_for(G)) void k_colsum(const float *x, int64_t
     case 1024 * 16 + F: M(1024, F, __VA_ARGS__); break;                                           \
     EVOX_BIG_4_8(M, __VA_ARGS__)
 
-#define EVOX_LAUNCH_PSO(GG, MM, MODEE) \
-    hipLaunchKernelGGL((k_pso<FN, GG, MM, MODEE>), dim3(grid), dim3(block_for(GG)), 0, s, a)
+#define EVOX_LAUNCH_PSO(GG, MM, MODEE)                                                                         \
+    do {                                                                                                       \
+        if (a.nt)                                                                                              \
+            hipLaunchKernelGGL((k_pso<FN, GG, MM, MODEE, true>), dim3(grid), dim3(block_for(GG)), 0, s, a);    \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_pso<FN, GG, MM, MODEE, false>), dim3(grid), dim3(block_for(GG)), 0, s, a);   \
+    } while (0)
 #define EVOX_LAUNCH_EVAL(GG, MM, VECC) \
     hipLaunchKernelGGL((k_eval<FN, GG, MM, VECC>), dim3(grid), dim3(block_for(GG)), 0, s, a)
 #define EVOX_LAUNCH_CSO(GG, MM, LOC) \

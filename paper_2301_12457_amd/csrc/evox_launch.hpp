@@ -15,6 +15,7 @@ enum PsoMode { PSO_EVAL = 0, PSO_FUSED = 1, PSO_MOVE = 2 };
 
 struct PsoArgs {
     float *x, *v, *p, *pf, *fit;
+    uint32_t *lag;  // [N] within a call: 1 where the personal best is the x row, not yet in p
     const float *gbest;
     int64_t N, D, ldx;
     float w, c1, c2, vmax, lb, ub;
@@ -23,6 +24,7 @@ struct PsoArgs {
     uint32_t t;  // generation whose move this launch performs
     SelSlots *slots;
     bool nt;     // streaming hint on row accesses
+    int64_t row0;  // first row of this launch
 };
 
 struct DeArgs {
@@ -228,7 +230,8 @@ struct CsoArgs {
     const float *xs;
 };
 
-hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &a, int grid, hipStream_t s);
+// One PSO pass over the whole swarm (a.row0 is set here).
+hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &a, hipStream_t s);
 // A whole n-generation PSO call in one block of kPsoSmallBlock threads, for
 // N D <= kPsoSmallElems, rows in at most 64 lanes and ldx <= kPsoSmallMaxLdx.
 constexpr int kPsoSmallBlock = 1024;
@@ -256,9 +259,10 @@ int occupancy_cso_t(Layout L, bool local);  // resident blocks per CU of k_cso
 hipError_t launch_eval(int fn, Layout L, bool vec, const EvalArgs &a, int grid, hipStream_t s);
 // Second pass of the selection: reduce and reset the slots, store the result
 // (best and/or the two outputs, each nullable) and copy the selected row of
-// `rows` (ldx floats) to row_out (nullable).
-hipError_t launch_select(SelSlots *slots, const float *rows, int64_t ldx, float *row_out,
-                         DevBest *best, float *best_f_out, int64_t *best_i_out, hipStream_t s);
+// `rows` (ldx floats), or of `rows_lag` where lag marks it (lag nullable), to
+// row_out (nullable).
+hipError_t launch_select(SelSlots *slots, const float *rows, const float *rows_lag, const uint32_t *lag, int64_t ldx,
+                         float *row_out, DevBest *best, float *best_f_out, int64_t *best_i_out, hipStream_t s);
 hipError_t launch_slots_init(SelSlots *slots, hipStream_t s);
 hipError_t launch_init(const InitArgs &a, hipStream_t s);
 hipError_t launch_philox_fill(uint32_t k0, uint32_t k1, uint32_t c1, uint32_t c2, uint32_t c3,

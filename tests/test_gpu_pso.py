@@ -176,3 +176,24 @@ def test_small_and_large_swarm_paths_agree(evox_gpu, ref):
         g.step(12)
         r.step(12)
         compare_state(g, r, 2, f"N = {N}")
+
+
+# rows of one wave, of several waves, and of several chunk pairs per lane, with
+# pitches that leave padding: the personal bests stay in x while a row improves
+# and reach pbest when it stops or the call ends
+LAG_CASES = [(2, 700, 65), (0, 300, 500), (1, 260, 1000), (4, 130, 2000), (3, 66, 4000), (2, 33, 8000), (0, 17, 16384),
+             (5, 9, 32768)]
+
+
+@pytest.mark.parametrize("fn,N,D", LAG_CASES)
+def test_personal_bests_after_calls_of_several_generations(evox_gpu, ref, fn, N, D):
+    lb, ub = {0: (-32.0, 32.0), 1: (-32.768, 32.768), 2: (-5.12, 5.12), 3: (-600.0, 600.0), 4: (-2.0, 2.0),
+              5: (-500.0, 500.0)}[fn]
+    print(f"pso lag fn={fn} N={N} D={D}", flush=True)
+    g, r = pair(evox_gpu, ref, fn, N, D, 23, lb, ub, vmax=0.2 * (ub - lb))
+    for n in (1, 2, 6):
+        g.step(n)
+        r.step(n)
+        compare_state(g, r, fn, f"after a call of {n}")
+        for name in ("x", "v", "pbest"):
+            assert not getattr(g, name)[:, D:].any(), f"{name} padding"
