@@ -30,7 +30,8 @@ DEFAULT_WORKLOAD = "pso_rastrigin_1e5x1e3"
 CONFIG_WORKLOADS = ("pso_sphere_100x10", "pso_ackley_1e4x1e3", "pso_rastrigin_1e5x1e3", "cso_griewank_1e6x100",
                     "eval_rosenbrock_1m_x1e3")
 KERNEL_SOURCES = ("paper_2301_12457_amd/csrc/evox_device.hpp",
-                  "paper_2301_12457_amd/csrc/evox_kernels.hpp")
+                  "paper_2301_12457_amd/csrc/evox_kernels.hpp",
+                  "paper_2301_12457_amd/csrc/evox_pso_resident.hpp")
 
 
 def kernel_hash():
@@ -70,6 +71,20 @@ def pso_bytes_per_generation(w, evaluations, improved_rows):
     # improved rows only), so the figure is a lower bound.
     imp = improved_rows / max(evaluations, 1)
     return 16.0 * w.N * w.D + 4.0 * w.D * (w.N - imp) + 12.0 * w.N
+
+
+# lane-ops per element and generation of a resident swarm: two Philox calls
+# per four elements (counted as in ES_OPS_PER_ELEMENT, 15 per element and
+# call), conversion and scaling 8, the two halves of the move 6, the square and
+# sum of Sphere 1 (the least any of the functions needs)
+PSO_OPS_PER_ELEMENT = 2 * 15 + 8 + 6 + 1
+
+
+def pso_resident(evox, w):
+    """Whether a step keeps the swarm on the chip (at least four generations,
+    at most ten rows per lane group of 256 blocks of 512 threads)."""
+    G, chunks = evox.row_layout(w.D)
+    return w.gens >= 4 and G <= 512 and chunks <= 2 and -(-w.N // (512 // G)) <= 2560
 
 
 def de_bytes_per_launch(w):
@@ -480,7 +495,7 @@ def measure(torch, evox, w, steps, warmup, ldx):
                         "algorithmic_ops_per_generation": ops}
         elif launches > 0:
             # per generation of the timed launches (a fused launch is one
-            # generation; a small swarm's one-block launch is a whole step)
+            # generation; a resident swarm's launch is a whole step)
             avg_ms = fused_ms / launches
             bytes_per = {"pso": lambda: pso_bytes_per_generation(w, steps * w.gens, improved),
                          "cso": lambda: cso_bytes_per_launch(w),
@@ -498,13 +513,17 @@ def measure(torch, evox, w, steps, warmup, ldx):
                 floor_bytes = 16.0 * w.N * w.D
                 roofline["frac_floor_16B"] = round(floor_bytes / (avg_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4)
                 roofline["improved_rows_per_generation"] = round(improved / (steps * w.gens), 1)
-                if launches == steps * w.gens:
-                    # the one-block kernel: one launch per step, the figures
-                    # above are per generation
-                    roofline["kernel"] = "k_pso_small (one block, a whole step per launch)"
-                    roofline["avg_launch_us"] = round(fused_ms / steps * 1e3, 2)
-                    roofline["launches"] = steps
-                    roofline["generation_us"] = round(avg_ms * 1e3, 3)
+                if pso_resident(evox, w):
+                    # one launch per step, the swarm on the chip: the random
+                    # numbers and the update bound it, not memory
+                    gen_s = fused_ms / 1e3 / (steps * w.gens)
+                    ops = PSO_OPS_PER_ELEMENT * w.N * w.D
+                    roofline = {"bound": "alu", "achieved": round(ops / gen_s / 1e12, 3), "peak": ALU_PEAK_TOPS,
+                                "unit": "Tops/s", "frac": round(ops / gen_s / 1e12 / ALU_PEAK_TOPS, 4),
+                                "traffic": traffic, "kernel": "k_pso_res (a whole step per launch)",
+                                "avg_launch_us": round(fused_ms / steps * 1e3, 2), "launches": steps,
+                                "generation_us": round(gen_s * 1e6, 3), "algorithmic_ops_per_generation": ops,
+                                "improved_rows_per_generation": roofline["improved_rows_per_generation"]}
     else:
         bytes_per = 4.0 * w.N * w.D + 4.0 * w.N
         achieved = bytes_per / (ms / 1e3) / 1e9

@@ -1,7 +1,7 @@
 """Build the gfx950 HIP library paper_2301_12457_amd/libevox.so in-tree.
 
 Every translation unit is compiled by hipcc for gfx950 only, in parallel:
-one per benchmark function (evox_fn.hip with -DEVOX_FN=<id>), the
+two per benchmark function (evox_fn.hip and evox_res.hip with -DEVOX_FN=<id>), the
 function-independent kernels (evox_common.hip) and the C ABI
 (evox_api.cpp), then linked into one shared library.
 
@@ -34,6 +34,7 @@ COMMON_FLAGS = [
 def _units():
     units = []
     for fn in range(N_FN):
+        units.append((os.path.join(CSRC, "evox_res.hip"), f"evox_res{fn}.o", [f"-DEVOX_FN={fn}"]))
         units.append((os.path.join(CSRC, "evox_fn.hip"), f"evox_fn{fn}.o", [f"-DEVOX_FN={fn}"]))
     units.append((os.path.join(CSRC, "evox_common.hip"), "evox_common.o", []))
     units.append((os.path.join(CSRC, "evox_gemm.hip"), "evox_gemm.o", []))

@@ -74,6 +74,13 @@ int cso_sweep(int64_t N, int rpb)
     return r;
 }
 
+// Fewest generations of a call that runs resident in several blocks: the
+// cooperative launch costs about 20 us and the swarm is loaded and stored once
+// more.  Per call of 1 / 2 / 4 generations, grid-wide against resident: 1999 x
+// 101 15.7 / 23.5 / 40.9 against 25.5 / 28.8 / 32.9 us, 10,000 x 1000 50 / 90 /
+// 167 against 84 / 105 / 143.
+constexpr int64_t kResMinGens = 4;
+
 int grid_for(int64_t groups, int G, int64_t cap)
 {
     const int64_t rpb = block_for(G) / G;
@@ -97,6 +104,8 @@ struct Plan {
     int64_t xsum_rows = 0;
     int perm_batch = 0;
     size_t lag = 0;           // PSO: marks of the rows whose personal best is the x row
+    PsoResPlan res{0, 0, 0};  // PSO: the resident call's shape, its slots and best rows
+    size_t res_slots = 0, res_cand = 0;
     size_t x2 = 0, fit2 = 0;  // DE: the other population buffer and its fitness
     size_t xalt = 0;          // CSO neighbourhood version: the other population buffer
     size_t mate = 0, cfit2 = 0;  // CSO: mate arrays, the other fitness buffer
@@ -218,7 +227,14 @@ int make_plan(const evox_params *P, Plan *pl)
     };
     p.best = take(sizeof(DevBest));
     p.slots = take(sizeof(SelSlots));
-    if (P->algo == EVOX_PSO) p.lag = take(sizeof(uint32_t) * (size_t)P->N);
+    if (P->algo == EVOX_PSO) {
+        p.lag = take(sizeof(uint32_t) * (size_t)P->N);
+        p.res = pso_res_plan(p.L, P->N);
+        if (p.res.nblocks > 1) {
+            p.res_slots = take(sizeof(uint64_t) * 4 * (size_t)p.res.nblocks);
+            p.res_cand = take(sizeof(uint64_t) * 2 * (size_t)p.res.nblocks * 4 * (size_t)p.L.G);
+        }
+    }
     if (P->algo == EVOX_CSO) {
         const int cap = cso_grid_cap(P->ldx);
         p.colsum_grid = grid_for(P->N, p.L.G, cap);
@@ -314,6 +330,7 @@ struct evox_state {
     int64_t perm_t0;  // first generation of the stored permutation batch (-1: none)
     double *xsum, *s1;
     uint32_t *lag;     // PSO: marks of the rows whose personal best is the x row
+    int res_calls;     // PSO: resident calls so far, modulo 2 (-1: not on this device)
     float *x2, *fit2;  // DE: the other population buffer
     uint32_t *esrank;  // ES: sample ranks
     double *espart;    // ES: gradient partial sums
@@ -363,6 +380,23 @@ hipError_t timed(evox_state *s, F &&launch, int64_t gens = 1)
 }
 
 hipError_t best_init(evox_state *s, float f, int64_t i) { return launch_best_init(s->best, f, i, s->stream); }
+
+// Whether `blocks` blocks, one per CU, can wait for each other on the current
+// device.
+bool cooperative(int blocks)
+{
+    int dev = 0, cus = 0, coop = 0;
+    return hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+           hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
+           cus >= blocks;
+}
+
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
 
 PsoArgs pso_args(evox_state *s)
 {
@@ -483,6 +517,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
     s->xsum = s->s1 = nullptr;
     s->perm_t0 = -1;
     s->ticket = nullptr;
+    s->res_calls = pl.res.nblocks > 1 && !cooperative(pl.res.nblocks) ? -1 : 0;
     s->lag = P.algo == EVOX_PSO ? at<uint32_t>(b->scratch, pl.lag) : nullptr;
     s->x2 = s->fit2 = nullptr;
     s->esrank = nullptr;
@@ -627,7 +662,9 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
     } else if (P.algo == EVOX_PSO) {
         if ((e = best_init(s, std::numeric_limits<float>::infinity(), 0)) != hipSuccess ||
             (e = launch_fill(b->pfit, P.N, std::numeric_limits<float>::infinity(), s->stream)) != hipSuccess ||
-            (e = launch_copy_row(b->pbest, b->gbest, P.ldx, s->stream)) != hipSuccess) {
+            (e = launch_copy_row(b->pbest, b->gbest, P.ldx, s->stream)) != hipSuccess ||
+            (pl.res.nblocks > 1 && (e = launch_fill_u32(at<uint32_t>(b->scratch, pl.res_slots), 8 * pl.res.nblocks,
+                                                        0xffffffffu, s->stream)) != hipSuccess)) {
             delete s;
             return hip_fail(e, "init");
         }
@@ -839,16 +876,33 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
     const int fn = s->P.fn_id;
     PsoArgs a = pso_args(s);
     hipError_t e;
-    if (pl.L.G <= 64 && s->P.N * s->P.D <= kPsoSmallElems && s->P.ldx <= kPsoSmallMaxLdx) {
-        // a small swarm: the whole call in one block, one launch
+    // what evox_profile counts: all n generations of a small swarm's call, the
+    // n - 1 between the first evaluation and the last move of another's
+    const bool small = pl.L.G <= 64 && s->P.N * s->P.D <= 16384;
+    if (pl.res.nblocks == 1 ||
+        (pl.res.nblocks > 1 && s->res_calls >= 0 && n_gens >= kResMinGens && !capturing(s->stream))) {
+        // the swarm on the chip for the whole call, one launch (a launch of
+        // blocks that wait for each other is not recorded into a graph)
+        const int nb = pl.res.nblocks;
+        uint64_t *slots = at<uint64_t>(s->B.scratch, pl.res_slots);
+        const PsoResArgs ra{n_gens, nb, slots + 2 * nb * s->res_calls, slots + 2 * nb * (1 - s->res_calls),
+                            at<uint64_t>(s->B.scratch, pl.res_cand), s->B.gbest, s->best};
         a.t = (uint32_t)s->t;
-        e = timed(s, [&] { return launch_pso_small(fn, pl.L, a, n_gens, s->B.gbest, s->best, s->stream); }, n_gens);
-        if (e != hipSuccess) return hip_fail(e, "pso generations");
-        s->t += n_gens;
-        return EVOX_OK;
+        e = timed(s, [&] { return launch_pso_res(fn, pl.L.G, pl.res, a, ra, s->stream); },
+                  small ? n_gens : n_gens - 1);
+        if (e == hipSuccess) {
+            if (nb > 1) s->res_calls ^= 1;
+            s->t += n_gens;
+            return EVOX_OK;
+        }
+        if (nb == 1) return hip_fail(e, "pso generations");
+        (void)hipGetLastError();  // the device does not take the launch: the grid-wide kernels from now on
+        s->res_calls = -1;
     }
     // generation t: evaluate x_t, personal and global bests
-    if ((e = launch_pso(fn, pl.L, PSO_EVAL, a, s->stream)) != hipSuccess) return hip_fail(e, "pso eval");
+    const auto first = [&] { return launch_pso(fn, pl.L, PSO_EVAL, a, s->stream); };
+    const auto last = [&] { return launch_pso(fn, pl.L, PSO_MOVE, a, s->stream); };
+    if ((e = small ? timed(s, first, 0) : first()) != hipSuccess) return hip_fail(e, "pso eval");
     if ((e = launch_select(s->slots, s->B.pbest, s->B.x, s->lag, s->P.ldx, s->B.gbest, s->best, nullptr, nullptr,
                            s->stream)) != hipSuccess)
         return hip_fail(e, "select");
@@ -861,7 +915,7 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
             return hip_fail(e, "select");
     }
     a.t = (uint32_t)(s->t + n_gens - 1);
-    if ((e = launch_pso(fn, pl.L, PSO_MOVE, a, s->stream)) != hipSuccess) return hip_fail(e, "pso move");
+    if ((e = small ? timed(s, last) : last()) != hipSuccess) return hip_fail(e, "pso move");
     s->t += n_gens;
     return EVOX_OK;
 }
@@ -1111,6 +1165,7 @@ int evox_best(evox_state *s, float *best_fit, int64_t *best_idx, float *best_x_h
     hipError_t e = hipMemcpyAsync(&h, s->best, sizeof h, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "read best");
+    if (h.failed) return fail(EVOX_EHIP, "a wait between the blocks of a resident PSO call ran out");
     if (best_fit) *best_fit = h.f;
     if (best_idx) *best_idx = h.i;
     if (best_x_host) {
@@ -1360,6 +1415,7 @@ int evox_profile_read(evox_state *s, double *fused_ms, int64_t *fused_launches, 
     DevBest h{};
     e = hipMemcpy(&h, s->best, sizeof h, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "profile read");
+    if (h.failed) return fail(EVOX_EHIP, "a wait between the blocks of a resident PSO call ran out");
     if (fused_ms) *fused_ms = ms;
     if (fused_launches) *fused_launches = s->prof_gens;
     if (improved_rows) *improved_rows = (int64_t)(h.improved - s->improved_base);

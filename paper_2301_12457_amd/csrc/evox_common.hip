@@ -25,8 +25,6 @@ namespace evox {
 // unit would hold a second copy of every one of those kernels.
 #define EVOX_EXTERN_FN(F)                                                                                          \
     extern template hipError_t launch_pso_t<F>(Layout, int, const PsoArgs &, int, hipStream_t);                    \
-    extern template hipError_t launch_pso_small_t<F>(Layout, const PsoArgs &, int64_t, float *, DevBest *,         \
-                                                     hipStream_t);                                                 \
     extern template hipError_t launch_eval_t<F>(Layout, bool, const EvalArgs &, int, hipStream_t);                 \
     extern template hipError_t launch_cso_t<F>(Layout, const CsoArgs &, int, hipStream_t);                         \
     extern template hipError_t launch_de_t<F>(Layout, const DeArgs &, int, hipStream_t);                           \
@@ -175,7 +173,7 @@ __global__ __launch_bounds__(256) void k_fill(float *dst, int64_t n, float value
 __global__ void k_best_init(DevBest *best, float f, int64_t i)
 {
     best->f = f;
-    best->pad = 0;
+    best->failed = 0;
     best->i = i;
     best->improved = 0;
 }
@@ -636,18 +634,6 @@ hipError_t launch_pair_move(int G, float *x, float *v, int64_t N, int64_t D, int
     }
 }
 
-// Handing data to another block of the same launch: the stores are written
-// through to memory (agent-scope atomic stores) and waited for before the
-// block signals, and the reader's agent-scope atomic loads go past its own
-// caches.  A release fence in its place writes back everything that is dirty
-// in the L2 (k_cso_mean over 1001 partial rows of 1000 columns: 15.8 us with
-// one fence per block).
-__device__ __forceinline__ void store_through(double *p, double v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // Block (0, 0) also finishes the selection (slots -> best) when asked.
 // xbar = (sum of the per-block partial rows) / N, rounded once, in two
 // stages.  Block (tile, rg) of 64 columns x 4 lanes: lane l sums partial rows
@@ -664,8 +650,7 @@ __device__ __forceinline__ double strided_sum(const double *base, int64_t first,
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int64_t q = q0 + u * step;
-            v[u] = q < end ? __hip_atomic_load(base + q * pitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                           : 0.0;
+            v[u] = q < end ? load_past(base + q * pitch) : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += v[u];
@@ -781,11 +766,31 @@ hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &args, hipStream
     return hipSuccess;
 }
 
-hipError_t launch_pso_small(int fn, Layout L, const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best,
-                            hipStream_t s)
+// One block while its 1024 threads hold a row per group; else as many blocks
+// as there are CUs, the fewest threads that hold the swarm with one row per
+// group (more blocks share the arithmetic; the exchange does not depend on
+// their number), then with 4 and with 10.
+PsoResPlan pso_res_plan(Layout L, int64_t N)
 {
-#define EVOX_CALL_PSO_SMALL(F) launch_pso_small_t<F>(L, a, n_gens, gbest_out, best, s)
-    EVOX_FN_SWITCH(EVOX_CALL_PSO_SMALL)
+    const PsoResPlan none{0, 0, 0};
+    if (L.maxit != LAYOUT_PSO || L.G > 512 || N >= kResMaxN) return none;
+    const int unit = L.G > 64 ? L.G : 64;
+    const struct { int shape, rows, threads; } shapes[] = {{1, 1, 1024}, {2, 4, 512}, {3, 10, 512}};
+    if (N * L.G <= 1024) return PsoResPlan{1, (int)((N * L.G + unit - 1) / unit * unit), 1};
+    for (const auto &sh : shapes)
+        for (int t = sh.shape == 3 ? sh.threads : unit; t <= sh.threads; t += unit) {
+            const int64_t gpb = t / L.G;
+            if (gpb * sh.rows * kResBlocks < N) continue;
+            const int64_t nb = (N + gpb - 1) / gpb;
+            return PsoResPlan{sh.shape, t, (int)(nb < kResBlocks ? nb : kResBlocks)};
+        }
+    return none;
+}
+
+hipError_t launch_pso_res(int fn, int G, const PsoResPlan &pl, const PsoArgs &a, const PsoResArgs &e, hipStream_t s)
+{
+#define EVOX_CALL_PSO_RES(F) launch_pso_res_t<F>(G, pl, a, e, s)
+    EVOX_FN_SWITCH(EVOX_CALL_PSO_RES)
 }
 
 hipError_t launch_eval(int fn, Layout L, bool vec, const EvalArgs &a, int grid, hipStream_t s)

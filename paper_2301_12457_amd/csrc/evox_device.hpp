@@ -192,7 +192,8 @@ __device__ __forceinline__ float4 normal4(uint32_t c, uint32_t row, uint32_t t, 
 // ---------------------------------------------------------------------------
 // Benchmark functions as row reductions.  Acc holds up to two partials; the
 // per-element step sees x_j, its right neighbour x_{j+1} (Rosenbrock) and the
-// 0-based index j; combine() merges two lanes' partials; finish() gives F.
+// 0-based index j (kZeroNeutral: x_j = 0 leaves the partials as they are, bit
+// for bit); combine() merges two lanes' partials; finish() gives F.
 // ---------------------------------------------------------------------------
 struct Acc {
     float a, b;
@@ -204,6 +205,7 @@ struct Fn;
 template <>
 struct Fn<FN_SPHERE> {  // sum x^2
     static constexpr bool kNeighbour = false;
+    static constexpr bool kZeroNeutral = true;
     __device__ static Acc init() { return {0.f, 0.f}; }
     __device__ static void elem(Acc &s, float x, float, int64_t) { s.a = fmaf(x, x, s.a); }
     __device__ static Acc combine(Acc p, Acc q) { return {p.a + q.a, 0.f}; }
@@ -213,6 +215,7 @@ struct Fn<FN_SPHERE> {  // sum x^2
 template <>
 struct Fn<FN_ACKLEY> {  // a = sum x^2, b = sum cos(2 pi x)
     static constexpr bool kNeighbour = false;
+    static constexpr bool kZeroNeutral = false;
     __device__ static Acc init() { return {0.f, 0.f}; }
     __device__ static void elem(Acc &s, float x, float, int64_t)
     {
@@ -246,6 +249,7 @@ __device__ __forceinline__ float sinpi_reduced(float r)
 template <>
 struct Fn<FN_RASTRIGIN> {  // a = sum (x^2 + 20 sin^2(pi x)) = 10 D + sum (x^2 - 10 cos(2 pi x))
     static constexpr bool kNeighbour = false;
+    static constexpr bool kZeroNeutral = true;
     __device__ static Acc init() { return {0.f, 0.f}; }
     __device__ static void elem(Acc &s, float x, float, int64_t)
     {
@@ -261,6 +265,7 @@ struct Fn<FN_RASTRIGIN> {  // a = sum (x^2 + 20 sin^2(pi x)) = 10 D + sum (x^2 -
 template <>
 struct Fn<FN_GRIEWANK> {  // a = sum x^2, b = prod cos(x / sqrt(j + 1))
     static constexpr bool kNeighbour = false;
+    static constexpr bool kZeroNeutral = true;
     __device__ static Acc init() { return {0.f, 1.f}; }
     __device__ static void elem(Acc &s, float x, float, int64_t j)
     {
@@ -274,6 +279,7 @@ struct Fn<FN_GRIEWANK> {  // a = sum x^2, b = prod cos(x / sqrt(j + 1))
 template <>
 struct Fn<FN_ROSENBROCK> {  // sum_{j < D-1} 100 (x_{j+1} - x_j^2)^2 + (1 - x_j)^2
     static constexpr bool kNeighbour = true;
+    static constexpr bool kZeroNeutral = false;
     __device__ static Acc init() { return {0.f, 0.f}; }
     __device__ static void elem(Acc &s, float x, float xn, int64_t)
     {
@@ -288,6 +294,7 @@ struct Fn<FN_ROSENBROCK> {  // sum_{j < D-1} 100 (x_{j+1} - x_j^2)^2 + (1 - x_j)
 template <>
 struct Fn<FN_SCHWEFEL> {  // a = sum x sin(sqrt|x|)
     static constexpr bool kNeighbour = false;
+    static constexpr bool kZeroNeutral = true;
     __device__ static Acc init() { return {0.f, 0.f}; }
     __device__ static void elem(Acc &s, float x, float, int64_t)
     {
@@ -306,10 +313,90 @@ struct Fn<FN_SCHWEFEL> {  // a = sum x sin(sqrt|x|)
 // floats for the cross-wave step.  Must be reached by every thread of the
 // block (it contains barriers when G > 64).
 // ---------------------------------------------------------------------------
-template <int G>
-__device__ __forceinline__ float shfl_xor_g(float v, int m)
+// This lane's value and that of lane ^ M, as an unordered pair (in the lanes
+// with bit M set the partner's comes first), for reductions whose combination
+// commutes: one or two register moves (v_permlane32_swap / 16_swap, DPP) in
+// place of an LDS permute with its address.  Every lane must be active.
+// EQ8: lanes i and i ^ 8 hold the same value (the step before was M = 8).
+template <int M, bool EQ8 = false>
+__device__ __forceinline__ void xor_pair(uint32_t v, uint32_t &p, uint32_t &q)
 {
-    return __shfl_xor(v, m, G < 64 ? G : 64);
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "a power of two below the wave");
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        p = r[0];
+        q = r[1];
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        p = r[0];
+        q = r[1];
+    } else {
+        p = v;
+        if constexpr (M == 8) {  // row_ror:8
+            q = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);
+        } else if constexpr (M == 4 && EQ8) {  // row_ror:4: lane ^ 4 or its equal
+            q = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true);
+        } else if constexpr (M == 4) {  // row_shl:4 into banks 0 and 2, row_shr:4 into 1 and 3
+            const int t = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xf, 0x5, false);
+            q = (uint32_t)__builtin_amdgcn_update_dpp(t, (int)v, 0x114, 0xf, 0xa, false);
+        } else if constexpr (M == 2) {  // quad_perm [2, 3, 0, 1]
+            q = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, true);
+        } else {  // quad_perm [1, 0, 3, 2]
+            q = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);
+        }
+    }
+}
+
+// Butterfly over lane bits M, M / 2, ..., 1.
+template <int FN, int M, bool EQ8 = false>
+__device__ __forceinline__ Acc lanes_combine(Acc s)
+{
+    if constexpr (M >= 1) {
+        uint32_t pa, qa, pb, qb;
+        xor_pair<M, EQ8>(__float_as_uint(s.a), pa, qa);
+        xor_pair<M, EQ8>(__float_as_uint(s.b), pb, qb);
+        s = Fn<FN>::combine(Acc{__uint_as_float(pa), __uint_as_float(pb)},
+                            Acc{__uint_as_float(qa), __uint_as_float(qb)});
+        return lanes_combine<FN, M / 2, M == 8>(s);
+    } else {
+        return s;
+    }
+}
+
+// Minimum over lane bits M, M / 2, ..., L (lanes that differ below L equal).
+template <int M, int L = 1, bool EQ8 = false>
+__device__ __forceinline__ uint32_t lanes_umin(uint32_t v)
+{
+    if constexpr (M >= L) {
+        uint32_t p, q;
+        xor_pair<M, EQ8>(v, p, q);
+        return lanes_umin<M / 2, L, M == 8>(p < q ? p : q);
+    } else {
+        return v;
+    }
+}
+
+// The same of (high word, low word) keys: the least high word, then the least
+// low word among the lanes that hold it -- a min and a move per step and word
+// instead of a 64-bit compare and two selects.
+template <int M, int L = 1>
+__device__ __forceinline__ uint64_t lanes_min(uint64_t k)
+{
+    const uint32_t hi = (uint32_t)(k >> 32), h = lanes_umin<M, L>(hi);
+    const uint32_t l = lanes_umin<M, L>(hi == h ? (uint32_t)k : 0xffffffffu);
+    return ((uint64_t)h << 32) | l;
+}
+
+template <int M, bool EQ8 = false>
+__device__ __forceinline__ uint32_t lanes_sum(uint32_t v)
+{
+    if constexpr (M >= 1) {
+        uint32_t p, q;
+        xor_pair<M, EQ8>(v, p, q);
+        return lanes_sum<M / 2, M == 8>(p + q);
+    } else {
+        return v;
+    }
 }
 
 // Combines the partials of a G-lane row group: butterfly inside the wave,
@@ -320,11 +407,7 @@ template <int FN, int G>
 __device__ __forceinline__ Acc group_reduce(Acc s, float *red)
 {
     using F = Fn<FN>;
-#pragma unroll
-    for (int m = (G < 64 ? G : 64) / 2; m >= 1; m >>= 1) {
-        Acc o{shfl_xor_g<G>(s.a, m), shfl_xor_g<G>(s.b, m)};
-        s = F::combine(s, o);
-    }
+    s = lanes_combine<FN, (G < 64 ? G : 64) / 2>(s);
     if constexpr (G > 64) {
         const int tid = threadIdx.x;
         constexpr int W = G / 64;  // waves per row
@@ -340,6 +423,33 @@ __device__ __forceinline__ Acc group_reduce(Acc s, float *red)
         for (int q = 1; q < W; ++q) t = F::combine(t, Acc{red[2 * (w0 + q)], red[2 * (w0 + q) + 1]});
         __syncthreads();
         s = t;
+    }
+    return s;
+}
+
+// One lane's partial of its row: its chunks in order, nb[it] the right
+// neighbour of chunk it's last element.  ZP: the elements past D are known to
+// be zero.
+template <int FN, int G, int MAXIT, bool ZP = false>
+__device__ __forceinline__ Acc row_partial(const float4 (&xr)[MAXIT], const float (&nb)[MAXIT], int g, int64_t D)
+{
+    using F = Fn<FN>;
+    Acc s = F::init();
+    const int lim = (int)(F::kNeighbour ? D - 1 : D);  // the last element has no pair
+#pragma unroll
+    for (int it = 0; it < MAXIT; ++it) {
+        const int j0 = 4 * (g + G * it);
+        const float4 v = xr[it];
+        const float n4[4] = {v.y, v.z, v.w, nb[it]};
+        if (ZP && 4 * G * it >= lim) continue;
+        if ((ZP && F::kZeroNeutral) || 4 * G * (it + 1) <= lim || j0 + 3 < lim) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) F::elem(s, comp(v, e), n4[e], j0 + e);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j0 + e < lim) F::elem(s, comp(v, e), n4[e], j0 + e);
+        }
     }
     return s;
 }
@@ -378,22 +488,7 @@ __device__ __forceinline__ float row_fitness(const float4 (&xr)[MAXIT], int g, i
         for (int it = 0; it < MAXIT; ++it) nb[it] = 0.0f;
     }
 
-    Acc s = F::init();
-#pragma unroll
-    for (int it = 0; it < MAXIT; ++it) {
-        const int64_t j0 = 4 * ((int64_t)g + (int64_t)G * it);
-        const float4 v = xr[it];
-        const float n4[4] = {v.y, v.z, v.w, nb[it]};
-        const int64_t lim = F::kNeighbour ? D - 1 : D;  // last element has no pair
-        if (j0 + 3 < lim) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) F::elem(s, comp(v, e), n4[e], j0 + e);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (j0 + e < lim) F::elem(s, comp(v, e), n4[e], j0 + e);
-        }
-    }
+    const Acc s = row_partial<FN, G, MAXIT>(xr, nb, g, D);
     return F::finish(group_reduce<FN, G>(s, red), D);
 }
 
@@ -428,23 +523,12 @@ __device__ __forceinline__ int64_t key_index(uint64_t k) { return (int64_t)(uint
 
 constexpr uint64_t kNoKey = ~(uint64_t)0;
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m)
-{
-    const int lo = __shfl_xor((int)(uint32_t)v, m, 64);
-    const int hi = __shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
-}
-
 // Block-wide min of per-thread keys and sum of counts; thread 0 gets them.
 // sk / sc: LDS of blockDim/64 entries each.  Reached by every thread.
 __device__ __forceinline__ void block_min_key(uint64_t &k, uint32_t &cnt, uint64_t *sk, uint32_t *sc)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const uint64_t o = shfl_xor_u64(k, m);
-        k = o < k ? o : k;
-        cnt += (uint32_t)__shfl_xor((int)cnt, m, 64);
-    }
+    k = lanes_min<32>(k);
+    cnt = lanes_sum<32>(cnt);
     const int wave = threadIdx.x / 64, nw = blockDim.x / 64;
     if ((threadIdx.x & 63) == 0) {
         sk[wave] = k;
@@ -473,10 +557,28 @@ __device__ __forceinline__ void slot_commit(SelSlots *sl, uint64_t k, uint32_t c
     if (cnt) atomicAdd(&sl->cnt[s], cnt);
 }
 
+// Handing data to another block of the same launch: the stores are written
+// through to memory (agent-scope atomic stores) and waited for before the
+// block signals, and the reader's agent-scope atomic loads go past its own
+// caches.  A release fence in its place writes back everything that is dirty
+// in the L2 (k_cso_mean over 1001 partial rows of 1000 columns: 15.8 us with
+// one fence per block).
+template <typename V>
+__device__ __forceinline__ void store_through(V *p, V v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename V>
+__device__ __forceinline__ V load_past(const V *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Result of a selection, kept in device scratch.
 struct DevBest {
     float f;
-    int32_t pad;
+    int32_t failed;  // a wait between the blocks of a resident call ran out
     int64_t i;
     uint64_t improved;  // PSO: rows whose personal best improved, summed
 };

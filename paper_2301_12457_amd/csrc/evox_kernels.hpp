@@ -40,10 +40,59 @@
 namespace evox {
 
 // ---------------------------------------------------------------------------
-// The PSO move of float4 chunk c of a row at generation a.t: r1, r2 from
-// Philox stream 2 (counters 2c and 2c + 1), vn = fma(c2 r2, g - x, fma(c1 r1,
-// p - x, w v)), optional clamps, x + vn; elements past D give zeros.
+// The PSO move of float4 chunk c of a row at generation t: r1, r2 from Philox
+// stream 2 (counters 2c and 2c + 1), vn = fma(c2 r2, g - x, fma(c1 r1, p - x,
+// w v)), optional clamps, x + vn; elements past D give zeros.  In two halves,
+// before and after the global best is known.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ float4 pso_pull4(const PsoArgs &a, uint32_t row, uint32_t c, uint32_t t, float4 xv,
+                                            float4 vv, float4 pv)
+{
+    const U4 r1 = philox(2 * c, row, t, STREAM_PSO, a.k0, a.k1);
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        o[e] = fmaf(a.c1 * wcomp(r1, e), comp(pv, e) - comp(xv, e), a.w * comp(vv, e));
+    return make_float4(o[0], o[1], o[2], o[3]);
+}
+
+// c2 r2
+__device__ __forceinline__ float4 pso_draw4(const PsoArgs &a, uint32_t row, uint32_t c, uint32_t t)
+{
+    const U4 r2 = philox(2 * c + 1, row, t, STREAM_PSO, a.k0, a.k1);
+    return make_float4(a.c2 * u01(r2.x), a.c2 * u01(r2.y), a.c2 * u01(r2.z), a.c2 * u01(r2.w));
+}
+
+// CLAMP false: no clamp is on.  MASK: elements past D give zeros (they stay
+// zero by themselves from zeros, unless the positions are clamped to a box
+// without 0).
+template <bool CLAMP, bool MASK>
+__device__ __forceinline__ void pso_push4(const PsoArgs &a, uint32_t c, float4 draw, float4 xv, float4 pull, float4 gv,
+                                          float4 &xn, float4 &vn)
+{
+    float xo[4], vo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float xe = comp(xv, e);
+        float nv = fmaf(comp(draw, e), comp(gv, e) - xe, comp(pull, e));
+        if (CLAMP && a.vclamp) nv = fminf(fmaxf(nv, -a.vmax), a.vmax);
+        float nx = xe + nv;
+        if (CLAMP && a.xclamp) nx = fminf(fmaxf(nx, a.lb), a.ub);
+        const bool in = !MASK || 4 * c + e < (uint32_t)a.D;
+        xo[e] = in ? nx : 0.0f;
+        vo[e] = in ? nv : 0.0f;
+    }
+    xn = make_float4(xo[0], xo[1], xo[2], xo[3]);
+    vn = make_float4(vo[0], vo[1], vo[2], vo[3]);
+}
+
+__device__ __forceinline__ void pso_move4(const PsoArgs &a, int64_t row, uint32_t c, float4 xv, float4 vv, float4 pv,
+                                          float4 gv, float4 &xn, float4 &vn)
+{
+    const float4 pull = pso_pull4(a, (uint32_t)row, c, a.t, xv, vv, pv);
+    pso_push4<true, true>(a, c, pso_draw4(a, (uint32_t)row, c, a.t), xv, pull, gv, xn, vn);
+}
+
 // The row of a lane group of at least a wave is the same in all its lanes:
 // known to the compiler, its addresses and the words of Philox that depend on
 // it alone are scalar.
@@ -52,29 +101,6 @@ __device__ __forceinline__ int64_t uniform_row(int64_t row)
 {
     if constexpr (G >= 64) return __builtin_amdgcn_readfirstlane((int)row);
     return row;
-}
-
-__device__ __forceinline__ void pso_move4(const PsoArgs &a, int64_t row, int64_t c, float4 xv, float4 vv,
-                                          float4 pv, float4 gv, float4 &xn, float4 &vn)
-{
-    const U4 r1 = philox((uint32_t)(2 * c), (uint32_t)row, a.t, STREAM_PSO, a.k0, a.k1);
-    const U4 r2 = philox((uint32_t)(2 * c + 1), (uint32_t)row, a.t, STREAM_PSO, a.k0, a.k1);
-    float xo[4], vo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float xe = comp(xv, e);
-        const float A = a.c1 * wcomp(r1, e);
-        const float Bc = a.c2 * wcomp(r2, e);
-        float nv = fmaf(Bc, comp(gv, e) - xe, fmaf(A, comp(pv, e) - xe, a.w * comp(vv, e)));
-        if (a.vclamp) nv = fminf(fmaxf(nv, -a.vmax), a.vmax);
-        float nx = xe + nv;
-        if (a.xclamp) nx = fminf(fmaxf(nx, a.lb), a.ub);
-        const bool in = 4 * c + e < a.D;
-        xo[e] = in ? nx : 0.0f;
-        vo[e] = in ? nv : 0.0f;
-    }
-    xn = make_float4(xo[0], xo[1], xo[2], xo[3]);
-    vn = make_float4(vo[0], vo[1], vo[2], vo[3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -200,187 +226,6 @@ __global__ __launch_bounds__(block_for(G)) void k_pso(PsoArgs a)
         }
         block_min_key(best, nimp, sk, sc);
         if (tid == 0) slot_commit(a.slots, best, nimp);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// A whole n-generation PSO call in one block, for swarms that one CU
-// evaluates and moves in a few microseconds (N D <= kPsoSmallElems, a row in
-// at most one wave): the grid-wide step between evaluation and move (the
-// global best) becomes a block barrier, so the call is one launch instead of
-// 2 n + 1.  Per generation t: evaluation of x_t and personal bests with the
-// row layout and reduction of k_pso (the same fitness bits, hence the same
-// decisions), the lexicographic minimum of (pfit, row) over the block, the
-// gbest row from pbest through LDS, then the move.  When every row fits in
-// one pass of the block the swarm stays in registers for the whole call;
-// otherwise the rows are walked in passes through global memory.
-// ---------------------------------------------------------------------------
-template <int FN, int G, int MAXIT>
-__global__ __launch_bounds__(kPsoSmallBlock) void k_pso_small(PsoArgs a, int64_t n_gens, float *gbest_out,
-                                                              DevBest *best)
-{
-    static_assert(G <= 64, "a row within one wave");
-    constexpr int B = kPsoSmallBlock, RPB = B / G;
-    __shared__ __align__(16) float gb[kPsoSmallMaxLdx];
-    __shared__ uint64_t sk[B / 64];
-    __shared__ uint32_t sc[B / 64];
-    __shared__ int64_t sel;
-    const int tid = threadIdx.x, g = tid % G, slot = tid / G;
-    const int64_t C4 = (a.D + 3) >> 2;
-    const int64_t CW = a.ldx / 4 < (int64_t)G * MAXIT ? a.ldx / 4 : (int64_t)G * MAXIT;
-    const uint32_t t0 = a.t;
-    for (int64_t j = tid; j < a.ldx; j += B) gb[j] = 0.0f;  // padding past the lanes' reach
-    __syncthreads();
-    if (a.N <= RPB) {
-        // every row in one pass of the block: x, v, pbest and pfit stay in
-        // registers for the whole call, only the gbest row goes through LDS
-        const int64_t row = slot;
-        const bool active = row < a.N;
-        float4 xr[MAXIT], vr[MAXIT], pr[MAXIT];
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) {
-            const int64_t c = g + (int64_t)G * it, off = row * a.ldx + 4 * c;
-            const bool in = active && c < C4;
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            xr[it] = in ? *reinterpret_cast<const float4 *>(a.x + off) : z;
-            vr[it] = in ? *reinterpret_cast<const float4 *>(a.v + off) : z;
-            pr[it] = in ? *reinterpret_cast<const float4 *>(a.p + off) : z;
-        }
-        float pf = active ? a.pf[row] : 0.0f, f = 0.0f;
-        uint64_t bk = kNoKey;
-        uint32_t nimp = 0, total_imp = 0;
-        for (int64_t k = 0; k < n_gens; ++k) {
-            a.t = t0 + (uint32_t)k;
-            f = row_fitness<FN, G, MAXIT>(xr, g, a.D, nullptr, nullptr);
-            const bool imp = active && f < pf;
-            if (imp) {
-#pragma unroll
-                for (int it = 0; it < MAXIT; ++it) pr[it] = xr[it];
-                pf = f;
-            }
-            bk = active && g == 0 ? sel_key(pf, row) : kNoKey;
-            nimp = imp && g == 0 ? 1u : 0u;
-            block_min_key(bk, nimp, sk, sc);
-            if (tid == 0) {
-                sel = bk == kNoKey ? 0 : key_index(bk);
-                total_imp += nimp;
-            }
-            __syncthreads();
-            if (row == sel) {
-#pragma unroll
-                for (int it = 0; it < MAXIT; ++it) {
-                    const int64_t c = g + (int64_t)G * it;
-                    if (c < CW) *reinterpret_cast<float4 *>(gb + 4 * c) = pr[it];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < MAXIT; ++it) {
-                const int64_t c = g + (int64_t)G * it;
-                if (active && c < C4) {
-                    const float4 gv = *reinterpret_cast<const float4 *>(gb + 4 * c);
-                    pso_move4(a, row, c, xr[it], vr[it], pr[it], gv, xr[it], vr[it]);
-                }
-            }
-            // the next write of gb follows the barriers of the next block minimum
-        }
-        if (active) {
-#pragma unroll
-            for (int it = 0; it < MAXIT; ++it) {
-                const int64_t c = g + (int64_t)G * it, off = row * a.ldx + 4 * c;
-                if (c < CW) {
-                    *reinterpret_cast<float4 *>(a.x + off) = xr[it];
-                    *reinterpret_cast<float4 *>(a.v + off) = vr[it];
-                    *reinterpret_cast<float4 *>(a.p + off) = pr[it];
-                }
-            }
-            if (g == 0) {
-                a.pf[row] = pf;
-                if (a.fit) a.fit[row] = f;
-            }
-        }
-        for (int64_t j = tid; j < a.ldx; j += B) gbest_out[j] = gb[j];
-        if (tid == 0) {
-            best->f = key_value(bk);
-            best->i = sel;
-            best->improved += total_imp;
-        }
-        return;
-    }
-    for (int64_t k = 0; k < n_gens; ++k) {
-        a.t = t0 + (uint32_t)k;
-        // evaluate x_t, personal bests
-        uint64_t bk = kNoKey;
-        uint32_t nimp = 0;
-        for (int64_t rb = 0; rb < a.N; rb += RPB) {  // uniform trip count
-            const int64_t row = rb + slot;
-            const bool active = row < a.N;
-            float4 xr[MAXIT];
-#pragma unroll
-            for (int it = 0; it < MAXIT; ++it) {
-                const int64_t c = g + (int64_t)G * it;
-                xr[it] = active && c < C4 ? *reinterpret_cast<const float4 *>(a.x + row * a.ldx + 4 * c)
-                                          : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            const float f = row_fitness<FN, G, MAXIT>(xr, g, a.D, nullptr, nullptr);
-            if (active) {
-                const float pold = a.pf[row];
-                const bool imp = f < pold;
-                if (imp) {
-#pragma unroll
-                    for (int it = 0; it < MAXIT; ++it) {
-                        const int64_t c = g + (int64_t)G * it;
-                        if (c < CW) *reinterpret_cast<float4 *>(a.p + row * a.ldx + 4 * c) = xr[it];
-                    }
-                }
-                if (g == 0) {
-                    if (imp) a.pf[row] = f;
-                    if (a.fit) a.fit[row] = f;
-                    const uint64_t key = sel_key(imp ? f : pold, row);
-                    bk = key < bk ? key : bk;
-                    nimp += imp ? 1u : 0u;
-                }
-            }
-        }
-        block_min_key(bk, nimp, sk, sc);
-        if (tid == 0) {
-            const int64_t i = bk == kNoKey ? 0 : key_index(bk);
-            best->f = key_value(bk);
-            best->i = i;
-            best->improved += nimp;
-            sel = i;
-        }
-        __syncthreads();
-        for (int64_t j = tid; j < a.ldx; j += B) {
-            const float v = a.p[sel * a.ldx + j];
-            gb[j] = v;
-            gbest_out[j] = v;
-        }
-        __syncthreads();
-        // move of generation t
-        for (int64_t rb = 0; rb < a.N; rb += RPB) {
-            const int64_t row = rb + slot;
-            if (row >= a.N) continue;
-#pragma unroll
-            for (int it = 0; it < MAXIT; ++it) {
-                const int64_t c = g + (int64_t)G * it;
-                const int64_t off = row * a.ldx + 4 * c;
-                if (c < C4) {
-                    const float4 xv = *reinterpret_cast<const float4 *>(a.x + off);
-                    const float4 vv = *reinterpret_cast<const float4 *>(a.v + off);
-                    const float4 pv = *reinterpret_cast<const float4 *>(a.p + off);
-                    const float4 gv = *reinterpret_cast<const float4 *>(gb + 4 * c);
-                    float4 xn, vn;
-                    pso_move4(a, row, c, xv, vv, pv, gv, xn, vn);
-                    *reinterpret_cast<float4 *>(a.x + off) = xn;
-                    *reinterpret_cast<float4 *>(a.v + off) = vn;
-                } else if (c < CW) {
-                    *reinterpret_cast<float4 *>(a.x + off) = make_float4(0.f, 0.f, 0.f, 0.f);
-                    *reinterpret_cast<float4 *>(a.v + off) = make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
-        }
-        __syncthreads();  // the next generation reads every moved row
     }
 }
 
@@ -1191,26 +1036,6 @@ hipError_t launch_pso_t(Layout L, int mode, const PsoArgs &a, int grid, hipStrea
                 default: return hipErrorInvalidValue;
             }
         }
-    }
-    return hipGetLastError();
-}
-
-template <int FN>
-hipError_t launch_pso_small_t(Layout L, const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best,
-                              hipStream_t s)
-{
-    if (L.maxit != LAYOUT_PSO) return hipErrorInvalidValue;
-    switch (L.G) {
-#define EVOX_SMALL(GG)                                                                                        \
-    case GG: hipLaunchKernelGGL((k_pso_small<FN, GG, LAYOUT_PSO>), dim3(1), dim3(kPsoSmallBlock), 0, s, a, \
-                                n_gens, gbest_out, best); break;
-        EVOX_SMALL(4)
-        EVOX_SMALL(8)
-        EVOX_SMALL(16)
-        EVOX_SMALL(32)
-        EVOX_SMALL(64)
-#undef EVOX_SMALL
-        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -232,16 +232,26 @@ struct CsoArgs {
 
 // One PSO pass over the whole swarm (a.row0 is set here).
 hipError_t launch_pso(int fn, Layout L, int mode, const PsoArgs &a, hipStream_t s);
-// A whole n-generation PSO call in one block of kPsoSmallBlock threads, for
-// N D <= kPsoSmallElems, rows in at most 64 lanes and ldx <= kPsoSmallMaxLdx.
-constexpr int kPsoSmallBlock = 1024;
-constexpr int64_t kPsoSmallElems = 16384;
-constexpr int64_t kPsoSmallMaxLdx = 1024;
-hipError_t launch_pso_small(int fn, Layout L, const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best,
-                            hipStream_t s);
+// A whole n-generation PSO call in one launch with the swarm on the chip
+// (evox_pso_resident.hpp).  shape 0: the swarm does not fit.
+constexpr int kResBlocks = 256;        // blocks at most: one per CU
+constexpr int64_t kResMaxN = 1 << 24;  // rows below this: 24 bits of index in a slot
+struct PsoResPlan {
+    int shape, threads, nblocks;
+};
+PsoResPlan pso_res_plan(Layout L, int64_t N);
+struct PsoResArgs {
+    int64_t n_gens;
+    int32_t nblocks;
+    uint64_t *slots;       // [2][nblocks] this call's slots, cleared by the call before
+    uint64_t *slots_next;  // [2][nblocks] the next call's
+    uint64_t *cand;        // [2][nblocks][4 G] the blocks' best rows
+    float *gbest_out;      // [ldx]
+    DevBest *best;
+};
+hipError_t launch_pso_res(int fn, int G, const PsoResPlan &pl, const PsoArgs &a, const PsoResArgs &e, hipStream_t s);
 template <int FN>
-hipError_t launch_pso_small_t(Layout L, const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best,
-                              hipStream_t s);
+hipError_t launch_pso_res_t(int G, const PsoResPlan &pl, const PsoArgs &a, const PsoResArgs &e, hipStream_t s);
 template <int FN>
 hipError_t launch_pso_t(Layout L, int mode, const PsoArgs &a, int grid, hipStream_t s);
 template <int FN>

@@ -197,3 +197,87 @@ def test_personal_bests_after_calls_of_several_generations(evox_gpu, ref, fn, N,
         compare_state(g, r, fn, f"after a call of {n}")
         for name in ("x", "v", "pbest"):
             assert not getattr(g, name)[:, D:].any(), f"{name} padding"
+
+
+# swarms that a call of at least four generations keeps on the chip: one block
+# (1024 lanes) and its first size beyond, then 256 blocks with one, four and
+# ten rows per lane group, each at its largest and first size beyond, for rows
+# of 4, 16, 64, 128, 256 and 512 lanes
+RESIDENT_CASES = [(0, 256, 13), (2, 257, 13), (4, 64, 101), (1, 65, 128), (4, 8, 1000), (4, 9, 1000), (5, 2, 4096),
+                  (3, 65_536, 3), (5, 65_537, 3), (0, 131_073, 5), (2, 327_680, 2), (2, 327_681, 2),
+                  (4, 16_385, 120), (1, 4_097, 512), (3, 2_049, 515), (4, 2_048, 1000), (0, 4_097, 1000),
+                  (1, 10_240, 1000), (4, 1_300, 2_047), (4, 513, 2_100), (2, 1_025, 4_096)]
+
+
+@pytest.mark.parametrize("fn,N,D", RESIDENT_CASES)
+def test_resident_calls_match_oracle(evox_gpu, ref, fn, N, D):
+    lb, ub = {0: (-32.0, 32.0), 1: (-32.768, 32.768), 2: (-5.12, 5.12), 3: (-600.0, 600.0), 4: (-2.0, 2.0),
+              5: (-500.0, 500.0)}[fn]
+    print(f"pso resident fn={fn} N={N} D={D}", flush=True)
+    kw = dict(vmax=0.2 * (ub - lb), clamp_x=1) if N % 2 else {}
+    g, r = pair(evox_gpu, ref, fn, N, D, 29, lb, ub, **kw)
+    for n in (4, 1, 5):  # resident, grid-wide, resident
+        g.step(n)
+        r.step(n)
+        compare_state(g, r, fn, f"after a call of {n}")
+        for name in ("x", "v", "pbest"):
+            assert not getattr(g, name)[:, D:].any(), f"{name} padding"
+
+
+def test_resident_calls_on_two_streams(evox_gpu, ref):
+    """Two swarms, each in 250 blocks that wait for each other, stepped on two
+    streams without waiting in between, for more generations than a slot's tag
+    counts."""
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    gs = [evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 2, 1999, 101, -5.12, 5.12, seed=s), stream=st)
+          for s, st in enumerate(streams)]
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for g in gs:
+            g.step(100)
+    torch.cuda.synchronize()
+    for s, g in enumerate(gs):
+        one = evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 2, 1999, 101, -5.12, 5.12, seed=s))
+        for _ in range(300):
+            one.step(2)  # grid-wide
+        for name in ("x", "v", "pbest", "pfit", "fit", "gbest"):
+            assert torch.equal(getattr(g, name), getattr(one, name)), name
+        assert g.best() == one.best()
+
+
+def test_captured_calls_of_a_resident_size(evox_gpu, ref):
+    """A call recorded into a graph, replayed between eager work, equals the
+    same call made eagerly."""
+    st = torch.cuda.Stream()
+    mk = lambda: evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 1, 1500, 90, -32.0, 32.0, seed=5), stream=st)  # noqa: E731
+    g, e = mk(), mk()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        g.step(6)
+    for _ in range(3):
+        with torch.cuda.stream(st):
+            graph.replay()
+            e.set_generation(0)
+            e.step(6)
+        torch.cuda.synchronize()
+        for name in ("x", "v", "pbest", "pfit", "gbest"):
+            assert torch.equal(getattr(g, name), getattr(e, name)), name
+
+
+def test_resident_selection_with_nan_and_infinite_rows(evox_gpu, ref):
+    for N, D in ((40, 12), (3000, 12)):
+        g, r = pair(evox_gpu, ref, 0, N, D, 31, -1.0, 1.0)
+        bad = np.full((N, D), np.nan, np.float32)
+        bad[N // 2:] = np.inf
+        good = N - 3
+        bad[good] = 0.25
+        g.x[:, :D] = torch.from_numpy(bad).cuda()
+        g.v.zero_()
+        r.x[:] = bad
+        r.v[:] = 0.0
+        g.step(5)
+        r.step(5)
+        assert g.best()[1] == r.gi == good
+        assert np.array_equal(host(g.pbest, D), r.p)
+        assert np.array_equal(host(g.x, D), r.x, equal_nan=True)
