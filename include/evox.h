@@ -204,8 +204,7 @@ int evox_eval_argmin(int fn_id, const float *X, int64_t N, int64_t D, int64_t ld
  * without a scratch argument.  Its selection slots live in a device array of
  * the library (EVOX_NOALLOC_SCRATCH_BYTES, 32 KiB, one copy per device, held
  * until the process ends); the call allocates nothing (no hipMalloc, hipFree
- * or allocating library routine) and resets the slots it uses with a kernel
- * before the evaluation.  Every call on a device shares that device's array:
+ * or allocating library routine) and sets the slots it reads in the same call.  Every call on a device shares that device's array:
  * calls that overlap on one device (concurrent streams or threads) race and
  * give wrong results.  The caller's current device must be the device of
  * hip_stream (EVOX_EINVAL otherwise); N, D, ldx as evox_eval_argmin, which

@@ -447,7 +447,7 @@ int cso_refresh(evox_state *s, bool refit)
     const Plan &pl = s->pl;
     hipError_t e;
     if (refit) {
-        EvalArgs ea{s->B.x, P.N, P.D, P.ldx, s->B.fit, nullptr, 4 * P.N * P.ldx > kStreamBytes};
+        EvalArgs ea{s->B.x, P.N, P.D, P.ldx, s->B.fit, nullptr, 4 * P.N * P.ldx > kStreamBytes, false, nullptr, nullptr};
         if ((e = launch_eval(P.fn_id, pl.L, true, ea, pl.grid, s->stream)) != hipSuccess)
             return hip_fail(e, "evaluate");
     }
@@ -736,8 +736,17 @@ int evox_state_destroy(evox_state *s)
     return EVOX_OK;
 }
 
+// The evaluation; with slots also the selection (best_f, best_i).  Up to
+// kEvalOneBlock rounds of rows in one block, the result written by the block:
+// one launch (a fifth round would cost more than the second launch); up to
+// kSlots blocks, each block's best in a slot of its own: no pass over the slots
+// before the evaluation.  A launch costs a caller of small
+// populations 3-4 us: 100 x 10 15.1 us with three launches, 8.1 with one; 2000 x
+// 100 15.0, 11.3 with two.
+constexpr int64_t kEvalOneBlock = 4;
+
 static int eval_common(int fn_id, const float *X, int64_t N, int64_t D, int64_t ldx, float *out,
-                       SelSlots *slots, hipStream_t st)
+                       SelSlots *slots, float *best_f, int64_t *best_i, hipStream_t st)
 {
     if (fn_id < 0 || fn_id >= FN_COUNT) return fail(EVOX_EINVAL, "unknown fn_id %d", fn_id);
     if (N < 0 || N >= ((int64_t)1 << 31)) return fail(EVOX_EINVAL, "N = %lld out of range", (long long)N);
@@ -746,24 +755,31 @@ static int eval_common(int fn_id, const float *X, int64_t N, int64_t D, int64_t 
     if (N > 0 && (!X || !out)) return fail(EVOX_EINVAL, "X and out are required");
     Layout L;
     if (!row_layout(D, LAYOUT_EVAL, &L)) return fail(EVOX_EINVAL, "no row layout for D = %lld", (long long)D);
-    const int grid = grid_for(N, L.G, kMaxGrid);
+    int grid = grid_for(N, L.G, kMaxGrid);
     if (N == 0) return EVOX_OK;
+    const bool one = slots && N <= kEvalOneBlock * (block_for(L.G) / L.G), own = slots && !one && grid <= kSlots;
+    if (one) grid = 1;
+    hipError_t e;
+    if (slots && !one && !own && (e = launch_slots_init(slots, st)) != hipSuccess) return hip_fail(e, "select init");
     const bool vec = (ldx & 3) == 0 && aligned16(X);
-    EvalArgs a{X, N, D, ldx, out, slots, 4 * N * ldx > kStreamBytes};
-    hipError_t e = launch_eval(fn_id, L, vec, a, grid, st);
+    EvalArgs a{X, N, D, ldx, out, slots, 4 * N * ldx > kStreamBytes, own, one ? best_f : nullptr, best_i};
+    e = launch_eval(fn_id, L, vec, a, grid, st);
     if (e != hipSuccess) return hip_fail(e, "evaluate");
-    return EVOX_OK;
+    if (!slots || one) return EVOX_OK;
+    e = own ? launch_select_own(slots, grid, best_f, best_i, st)
+            : launch_select(slots, nullptr, nullptr, nullptr, 0, nullptr, nullptr, best_f, best_i, st);
+    return e == hipSuccess ? EVOX_OK : hip_fail(e, "select");
 }
 
 int evox_eval(int fn_id, const float *X, int64_t N, int64_t D, float *out, void *hip_stream)
 {
-    return eval_common(fn_id, X, N, D, D, out, nullptr, (hipStream_t)hip_stream);
+    return eval_common(fn_id, X, N, D, D, out, nullptr, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 int evox_eval_ld(int fn_id, const float *X, int64_t N, int64_t D, int64_t ldx, float *out,
                  void *hip_stream)
 {
-    return eval_common(fn_id, X, N, D, ldx, out, nullptr, (hipStream_t)hip_stream);
+    return eval_common(fn_id, X, N, D, ldx, out, nullptr, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 size_t evox_eval_argmin_scratch_bytes(int64_t)
@@ -784,16 +800,10 @@ int evox_eval_argmin(int fn_id, const float *X, int64_t N, int64_t D, int64_t ld
     SelSlots *slots = at<SelSlots>(scratch, 0);
     hipStream_t st = (hipStream_t)hip_stream;
     // validate before enqueueing anything
-    int rc = eval_common(fn_id, nullptr, 0, D, ldx, nullptr, nullptr, st);
+    int rc = eval_common(fn_id, nullptr, 0, D, ldx, nullptr, nullptr, nullptr, nullptr, st);
     if (rc != EVOX_OK) return rc;
     if (!X || !out) return fail(EVOX_EINVAL, "X and out are required");
-    hipError_t e = launch_slots_init(slots, st);
-    if (e != hipSuccess) return hip_fail(e, "select init");
-    rc = eval_common(fn_id, X, N, D, ldx, out, slots, st);
-    if (rc != EVOX_OK) return rc;
-    e = launch_select(slots, nullptr, nullptr, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st);
-    if (e != hipSuccess) return hip_fail(e, "select");
-    return EVOX_OK;
+    return eval_common(fn_id, X, N, D, ldx, out, slots, best_fit_dev, best_idx_dev, st);
 }
 
 }  // extern "C"
@@ -842,7 +852,7 @@ int evox_eval_argmin_noalloc(int fn_id, const float *X, int64_t N, int64_t D, in
                     EVOX_NOALLOC_SCRATCH_BYTES);
     hipStream_t st = (hipStream_t)hip_stream;
     // validate before enqueueing anything
-    int rc = eval_common(fn_id, nullptr, 0, D, ldx, nullptr, nullptr, st);
+    int rc = eval_common(fn_id, nullptr, 0, D, ldx, nullptr, nullptr, nullptr, nullptr, st);
     if (rc != EVOX_OK) return rc;
     if (!X || !out) return fail(EVOX_EINVAL, "X and out are required");
     int dev = -1;
@@ -857,12 +867,7 @@ int evox_eval_argmin_noalloc(int fn_id, const float *X, int64_t N, int64_t D, in
     void *ptr = nullptr;
     if ((rc = noalloc_scratch(dev, &ptr)) != EVOX_OK) return rc;
     SelSlots *slots = static_cast<SelSlots *>(ptr);
-    if ((e = launch_slots_init(slots, st)) != hipSuccess) return hip_fail(e, "select init");
-    rc = eval_common(fn_id, X, N, D, ldx, out, slots, st);
-    if (rc != EVOX_OK) return rc;
-    if ((e = launch_select(slots, nullptr, nullptr, nullptr, 0, nullptr, nullptr, best_fit_dev, best_idx_dev, st)) != hipSuccess)
-        return hip_fail(e, "select");
-    return EVOX_OK;
+    return eval_common(fn_id, X, N, D, ldx, out, slots, best_fit_dev, best_idx_dev, st);
 }
 
 int evox_pso_step(evox_state *s, int64_t n_gens)

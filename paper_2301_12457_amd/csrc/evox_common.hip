@@ -138,6 +138,30 @@ hipError_t launch_select(SelSlots *slots, const float *rows, const float *rows_l
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_select_own(const SelSlots *sl, int n, float *bf_out, int64_t *bi_out)
+{
+    __shared__ uint64_t sk[4];
+    __shared__ uint32_t sc[4];
+    constexpr int R = kSlots / 256;
+    uint64_t kq[R], k = kNoKey;  // all loads in flight
+    uint32_t none = 0;
+#pragma unroll
+    for (int u = 0; u < R; ++u) kq[u] = sl->key[threadIdx.x + 256 * u < (unsigned)n ? threadIdx.x + 256 * u : 0];
+#pragma unroll
+    for (int u = 0; u < R; ++u) k = kq[u] < k ? kq[u] : k;
+    block_min_key(k, none, sk, sc);
+    if (threadIdx.x == 0) {
+        *bf_out = key_value(k);
+        *bi_out = key_index(k);
+    }
+}
+
+hipError_t launch_select_own(const SelSlots *slots, int n, float *best_f_out, int64_t *best_i_out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_select_own, dim3(1), dim3(256), 0, s, slots, n, best_f_out, best_i_out);
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(1024) void k_slots_init(SelSlots *sl)
 {
     for (int q = threadIdx.x; q < kSlots; q += blockDim.x) {

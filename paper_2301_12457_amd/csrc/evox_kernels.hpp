@@ -231,7 +231,8 @@ __global__ __launch_bounds__(block_for(G)) void k_pso(PsoArgs a)
 
 // ---------------------------------------------------------------------------
 // Problem.evaluate over any row pitch / alignment; optionally folds each
-// block's best (fitness, row) into a selection slot.  VEC: 16-byte aligned
+// block's best (fitness, row) into a selection slot, or writes it to a slot of
+// the block's own, or as the result (EvalArgs).  VEC: 16-byte aligned
 // rows, float4 loads.
 // ---------------------------------------------------------------------------
 template <int FN, int G, int MAXIT, bool VEC>
@@ -279,7 +280,16 @@ __global__ __launch_bounds__(block_for(G)) void k_eval(EvalArgs a)
     }
     if (a.slots) {
         block_min_key(best, none, sk, sc);
-        if (tid == 0) slot_commit(a.slots, best, 0);
+        if (tid == 0) {
+            if (a.best_f) {  // the only block: its best is the population's
+                *a.best_f = key_value(best);
+                *a.best_i = key_index(best);
+            } else if (a.own_slot) {
+                a.slots->key[blockIdx.x] = best;
+            } else {
+                slot_commit(a.slots, best, 0);
+            }
+        }
     }
 }
 

@@ -189,6 +189,9 @@ struct EvalArgs {
     float *out;
     SelSlots *slots;  // nullable: no selection
     bool nt;          // streaming hint on row accesses
+    bool own_slot;    // every block has a slot of its own (at most kSlots blocks): stored, not folded
+    float *best_f;    // one block: the selection's result (null: slots)
+    int64_t *best_i;
 };
 
 struct InitArgs {
@@ -273,6 +276,8 @@ hipError_t launch_eval(int fn, Layout L, bool vec, const EvalArgs &a, int grid, 
 // row_out (nullable).
 hipError_t launch_select(SelSlots *slots, const float *rows, const float *rows_lag, const uint32_t *lag, int64_t ldx,
                          float *row_out, DevBest *best, float *best_f_out, int64_t *best_i_out, hipStream_t s);
+// The same over the first n slots, which their blocks own (no reset).
+hipError_t launch_select_own(const SelSlots *slots, int n, float *best_f_out, int64_t *best_i_out, hipStream_t s);
 hipError_t launch_slots_init(SelSlots *slots, hipStream_t s);
 hipError_t launch_init(const InitArgs &a, hipStream_t s);
 hipError_t launch_philox_fill(uint32_t k0, uint32_t k1, uint32_t c1, uint32_t c2, uint32_t c3,

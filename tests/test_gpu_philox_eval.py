@@ -124,3 +124,31 @@ def test_stream_copy(evox_gpu, n):
     dst = torch.zeros(n + 8, device="cuda")
     evox_gpu.evox_copy(src, dst, n)
     assert torch.equal(dst[:n], src[:n]) and torch.all(dst[n:] == 0)
+
+
+# one block's rounds of rows and the first size beyond, one slot per block and
+# the first size beyond, for rows of 4 lanes (64 per block) and of a wave (4),
+# aligned and not; the scratch holds whatever an earlier use left
+SELECTION_SIZES = [(1, 10), (256, 10), (257, 10), (131_072, 9), (131_073, 9), (16, 1000), (17, 999), (8_192, 997),
+                   (8_193, 1000), (3, 20_000)]
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("N,D", SELECTION_SIZES)
+def test_selection_at_the_edges_of_its_routes(evox_gpu, N, D, noalloc):
+    print(f"selection N={N} D={D} noalloc={noalloc}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N + D)
+    X = torch.empty((N, D), device="cuda").uniform_(-5.0, 5.0, generator=gen)
+    out, bf = torch.empty(N, device="cuda"), torch.empty(1, device="cuda")
+    bi = torch.empty(1, dtype=torch.int64, device="cuda")
+    for junk, best in ((0, N - 1), (255, N // 2), (17, 0)):
+        X[best] = 0.01
+        if best < N - 1:
+            X[N - 1] = 0.01  # a tie: the lower index
+        scratch = torch.full((evox_gpu.evox_eval_argmin_scratch_bytes(N),), junk, dtype=torch.uint8, device="cuda")
+        if noalloc:
+            evox_gpu.evox_eval_argmin_noalloc(0, X, N, D, D, out, bf, bi)
+        else:
+            evox_gpu.evox_eval_argmin(0, X, N, D, D, out, bf, bi, scratch)
+        assert int(bi) == best and float(bf) == float(out[best]) == float(out.min())
+        X[best] = 4.0
