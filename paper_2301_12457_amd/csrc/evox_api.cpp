@@ -96,6 +96,40 @@ T *at_off(void *base, size_t off)
     return reinterpret_cast<T *>(static_cast<char *>(base) + off);
 }
 
+// Scratch of the non-dominated sorting of n points with M objectives,
+// placed from `off` on: the coarse order, the points' objectives in it and
+// the chunks' ranges, dominator bits and the front search's state, the
+// front-ordered list, front offsets, the per-objective positions and orders,
+// the list length.
+struct NsgaSortScratch {
+    size_t ord, hist, fs, fr, range, W, ptr, mask, list, foff, pos, sorted, len, end;
+};
+NsgaSortScratch nsga_sort_layout(int64_t n, int32_t M, size_t off)
+{
+    NsgaSortScratch l{};
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off = round256(off + bytes);
+        return at;
+    };
+    const size_t chunks = ((size_t)n + kNsgaChunk - 1) / kNsgaChunk, P = M <= 4 ? 4 : 8;
+    l.ord = take(4 * (size_t)n);
+    l.hist = take(4 * (kNsgaSplit + 1));
+    l.fs = take(4 * P * kNsgaChunk * chunks);
+    l.fr = take(4 * (size_t)nsga_rest(M) * kNsgaChunk * chunks);
+    l.range = take(4 * 2 * chunks);
+    l.W = take(16 * 2 * kNsgaChunk * chunks * chunks);
+    l.ptr = take(4 * (size_t)n);
+    l.mask = take(4 * 2 * (kNsgaChunk / 32) * chunks);
+    l.list = take(4 * (size_t)n);
+    l.foff = take(4 * ((size_t)n + 1));
+    l.pos = take(4 * (size_t)M * (size_t)n);
+    l.sorted = take(4 * (size_t)M * (size_t)n);
+    l.len = take(4 * (size_t)kNsgaPeelBatch);
+    l.end = off;
+    return l;
+}
+
 struct Plan {
     Layout L{0, 0, 0};
     int grid = 0, cso_grid = 0, cso_sweep = 0, colsum_grid = 0, bits = 0;
@@ -118,39 +152,19 @@ struct Plan {
     int64_t mae_mu = 0, mae_kp = 0, mae_ldf = 0;
     // NSGA-II: offspring, survivors' rows, merged objectives / fronts /
     // crowding, the sorting scratch, survivor flags and their prefix sums
-    size_t ns_q = 0, ns_x2 = 0, ns_fr = 0, ns_frontr = 0, ns_crowdr = 0, ns_keep = 0, ns_pre = 0, ns_sums = 0;
-    size_t ns_cnt = 0, ns_list = 0, ns_foff = 0, ns_pos = 0, ns_sorted = 0, ns_len = 0;
+    size_t ns_q = 0, ns_x2 = 0, ns_fr = 0, ns_frontr = 0, ns_crowdr = 0, ns_keep = 0, ns_pre = 0;
+    NsgaSortScratch ns_sort{};
     size_t total = 0;
 };
-
-// Scratch of the non-dominated sorting of n points with M objectives,
-// placed from `off` on: counts, the front-ordered list, front offsets, the
-// per-objective positions and orders, the list length.
-struct NsgaSortScratch {
-    size_t cnt, list, foff, pos, sorted, len, end;
-};
-NsgaSortScratch nsga_sort_layout(int64_t n, int32_t M, size_t off)
-{
-    NsgaSortScratch l{};
-    auto take = [&](size_t bytes) {
-        const size_t at = off;
-        off = round256(off + bytes);
-        return at;
-    };
-    l.cnt = take(4 * (size_t)n);
-    l.list = take(4 * (size_t)n);
-    l.foff = take(4 * ((size_t)n + 1));
-    l.pos = take(4 * (size_t)M * (size_t)n);
-    l.sorted = take(4 * (size_t)M * (size_t)n);
-    l.len = take(4 * (size_t)kNsgaPeelBatch);
-    l.end = off;
-    return l;
-}
 
 NsgaSortArgs nsga_sort_args(void *scratch, const NsgaSortScratch &l, const float *F, int64_t n, int32_t M,
                             int32_t *front, double *crowd)
 {
-    return NsgaSortArgs{F, n, M, front, crowd, at_off<uint32_t>(scratch, l.cnt), at_off<int32_t>(scratch, l.list),
+    return NsgaSortArgs{F, n, M, front, crowd, at_off<int32_t>(scratch, l.ord),
+                        at_off<uint32_t>(scratch, l.hist), at_off<float>(scratch, l.fs), at_off<float>(scratch, l.fr),
+                        at_off<float>(scratch, l.range), at_off<uint4>(scratch, l.W),
+                        at_off<uint32_t>(scratch, l.ptr), at_off<uint32_t>(scratch, l.mask), 0,
+                        at_off<int32_t>(scratch, l.list),
                         at_off<int32_t>(scratch, l.foff), at_off<int32_t>(scratch, l.pos),
                         at_off<int32_t>(scratch, l.sorted), n, at_off<uint32_t>(scratch, l.len)};
 }
@@ -297,15 +311,8 @@ int make_plan(const evox_params *P, Plan *pl)
         p.ns_crowdr = take(sizeof(double) * R);
         p.ns_keep = take(sizeof(int32_t) * R);
         p.ns_pre = take(sizeof(int32_t) * R);
-        p.ns_sums = take(sizeof(int32_t) * ((R + 1023) / 1024));
-        const NsgaSortScratch l = nsga_sort_layout((int64_t)R, P->n_obj, off);
-        p.ns_cnt = l.cnt;
-        p.ns_list = l.list;
-        p.ns_foff = l.foff;
-        p.ns_pos = l.pos;
-        p.ns_sorted = l.sorted;
-        p.ns_len = l.len;
-        off = l.end;
+        p.ns_sort = nsga_sort_layout((int64_t)R, P->n_obj, off);
+        off = p.ns_sort.end;
     }
     p.total = off;
     *pl = p;
@@ -586,14 +593,11 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         float *FR = at<float>(b->scratch, pl.ns_fr);
         int32_t *frontR = at<int32_t>(b->scratch, pl.ns_frontr);
         double *crowdR = at<double>(b->scratch, pl.ns_crowdr);
-        s->ns_sort = NsgaSortArgs{FR, R, P.n_obj, frontR, crowdR, at<uint32_t>(b->scratch, pl.ns_cnt),
-                                  at<int32_t>(b->scratch, pl.ns_list), at<int32_t>(b->scratch, pl.ns_foff),
-                                  at<int32_t>(b->scratch, pl.ns_pos), at<int32_t>(b->scratch, pl.ns_sorted), R,
-                                  at<uint32_t>(b->scratch, pl.ns_len)};
+        s->ns_sort = nsga_sort_args(b->scratch, pl.ns_sort, FR, R, P.n_obj, frontR, crowdR);
         s->ns_sel = NsgaSelArgs{b->x, at<float>(b->scratch, pl.ns_q), P.N, P.ldx, P.n_obj, FR, frontR, crowdR,
                                 s->ns_sort.list, at<int32_t>(b->scratch, pl.ns_keep),
                                 at<int32_t>(b->scratch, pl.ns_pre), s->ns_sort.pos,
-                                at<int32_t>(b->scratch, pl.ns_sums), at<float>(b->scratch, pl.ns_x2), b->obj,
+                                at<float>(b->scratch, pl.ns_x2), b->obj,
                                 b->front, b->crowd};
     }
     if (P.algo == EVOX_CSO) {
@@ -654,7 +658,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         init.crowd = b->crowd;
         NsgaSortResult r;
         if ((e = launch_fill(at<float>(b->scratch, pl.ns_q), P.N * P.ldx, 0.0f, s->stream)) != hipSuccess ||
-            (e = launch_nsga_dtlz1(b->x, P.N, P.D, P.ldx, P.n_obj, b->obj, s->stream)) != hipSuccess ||
+            (e = launch_nsga_dtlz1(b->x, P.N, P.D, P.ldx, P.n_obj, nullptr, 0, b->obj, nullptr, s->stream)) != hipSuccess ||
             (e = nsga_sort(init, P.N, &r, s->stream)) != hipSuccess) {
             delete s;
             return hip_fail(e, "init");
@@ -1042,25 +1046,30 @@ int nsga_generations(evox_state *s, int64_t n_gens)
     const evox_params &P = s->P;
     const int32_t M = P.n_obj;
     hipError_t e;
+    // the population alternates between the caller's x and the survivors' buffer
+    float *cur = s->B.x, *other = at<float>(s->B.scratch, s->pl.ns_x2);
     for (int64_t k = 0; k < n_gens; ++k) {
         const uint32_t t = (uint32_t)(s->t + k);
-        NsgaVarArgs va{s->B.x, P.N, P.D, P.ldx, s->B.front, s->B.crowd, at<float>(s->B.scratch, s->pl.ns_q),
+        NsgaVarArgs va{cur, P.N, P.D, P.ldx, s->B.front, s->B.crowd, at<float>(s->B.scratch, s->pl.ns_q),
                        (double)P.sbx_eta,
                        (double)P.pm_eta, s->k0, s->k1, t};
+        NsgaSelArgs sel = s->ns_sel;
+        sel.X = cur;
+        sel.X2 = other;
         NsgaSortResult r;
         if ((e = launch_nsga_var(va, s->stream)) != hipSuccess) return hip_fail(e, "variation");
-        if ((e = launch_stream_copy(s->B.obj, (float *)s->ns_sort.F, P.N * M, s->stream)) != hipSuccess)
-            return hip_fail(e, "merge");
-        if ((e = launch_nsga_dtlz1(s->ns_sel.Q, P.N, P.D, P.ldx, M, (float *)s->ns_sort.F + P.N * M, s->stream)) !=
+        if ((e = launch_nsga_dtlz1(sel.Q, P.N, P.D, P.ldx, M, s->B.obj, P.N, (float *)s->ns_sort.F,
+                                   s->ns_sort.hist, s->stream)) !=
             hipSuccess)
             return hip_fail(e, "objectives");
-        if ((e = timed(s, [&] { return nsga_count(s->ns_sort, s->stream); })) != hipSuccess ||
+        if ((e = timed(s, [&] { return nsga_relate(s->ns_sort, s->stream); })) != hipSuccess ||
             (e = nsga_fronts(s->ns_sort, P.N, &r, s->stream)) != hipSuccess)
             return hip_fail(e, "non-dominated sorting");
-        if ((e = launch_nsga_select(s->ns_sel, r, s->stream)) != hipSuccess) return hip_fail(e, "selection");
-        if ((e = launch_stream_copy(s->ns_sel.X2, s->B.x, P.N * P.ldx, s->stream)) != hipSuccess)
-            return hip_fail(e, "survivors");
+        if ((e = launch_nsga_select(sel, r, s->stream)) != hipSuccess) return hip_fail(e, "selection");
+        std::swap(cur, other);
     }
+    if (cur != s->B.x && (e = launch_stream_copy(cur, s->B.x, P.N * P.ldx, s->stream)) != hipSuccess)
+        return hip_fail(e, "survivors");
     s->t += n_gens;
     return EVOX_OK;
 }

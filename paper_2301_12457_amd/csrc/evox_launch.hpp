@@ -108,7 +108,13 @@ int occupancy_gemm_nt_thin(int64_t M);  // resident blocks per CU of the tile sh
 // NSGA-II on DTLZ1.
 constexpr int kNsgaMaxM = 8;          // objectives
 constexpr int64_t kNsgaMaxN = 32768;  // population (the merged population is 2N)
-constexpr int kNsgaPeelBatch = 8;     // fronts peeled per host round trip
+constexpr int kNsgaPeelBatch = 8;     // fronts searched for per host round trip
+constexpr int kNsgaChunk = 256;       // positions per chunk of the coarse order
+constexpr int kNsgaMaxPoints = 65536; // points sorted at most
+constexpr int kNsgaSplit = 1024;      // sampled splitters of the coarse order
+constexpr uint32_t kNsgaNoWord = 0xffffffffu;
+// floats per point of the objectives without the first
+constexpr int nsga_rest(int M) { return M <= 2 ? 1 : M == 3 ? 2 : M <= 5 ? 4 : 8; }
 struct NsgaVarArgs {
     const float *X;        // parents [N][ldx]
     int64_t N, D, ldx;
@@ -124,12 +130,21 @@ struct NsgaSortArgs {
     int32_t M;
     int32_t *front;        // [n] out: front index, -1 past the fronts needed
     double *crowd;         // [n] out: crowding distance within the front
-    uint32_t *cnt;         // [n] dominator counts
+    int32_t *ord;          // [n] the points in the coarse order of the first objective
+    uint32_t *hist;        // [kNsgaSplit + 1] counts of the coarse order's buckets, zero before a sort
+    float *Fs;             // [chunks * 256][4 or 8] their objectives, padded
+    float *Fr;             // [chunks * 256][nsga_rest(M)] the same without the first
+    float *range;          // [chunks][2] least and greatest first objective of a chunk
+    uint4 *W;              // [chunks][2 chunks][256] dominator bits, 128 positions each
+    uint32_t *ptr;         // [n] places in the coarse order, then the group of four words a point
+                           // waits on, or kNsgaNoWord
+    uint32_t *mask;        // [2][chunks * 8] unassigned points, alternating by front
+    int64_t chunks;        // set where the arrays are used
     int32_t *list;         // [n] points front by front
     int32_t *foff;         // [n + 1] first list position of each front
     int32_t *pos, *sorted; // [M][cap] order within the front per objective
     int64_t cap;           // >= n
-    uint32_t *len;         // [kNsgaPeelBatch] sizes of the fronts of a peeling batch
+    uint32_t *len;         // [kNsgaPeelBatch] sizes of the fronts of a batch
 };
 struct NsgaSortResult {
     int32_t fronts;        // fronts assigned
@@ -146,20 +161,22 @@ struct NsgaSelArgs {
     const int32_t *list;   // [2N] from the sort
     int32_t *keep, *pre;   // [2N]
     int32_t *rank;         // [2N] last-front ranks (the sort's free per-objective positions)
-    int32_t *sums;         // [ceil(2N / 1024)] block sums of the survivor prefix sums
     float *X2;             // [N][ldx] survivors' rows
     float *F;              // [N][M]
     int32_t *front;        // [N]
     double *crowd;         // [N]
 };
 hipError_t launch_nsga_var(const NsgaVarArgs &a, hipStream_t s);
-hipError_t launch_nsga_dtlz1(const float *X, int64_t n, int64_t D, int64_t ldx, int32_t M, float *F, hipStream_t s);
+// F = the objectives Fold [nold][M], then those of the n rows of X; clears the
+// counts hist (nullable).
+hipError_t launch_nsga_dtlz1(const float *X, int64_t n, int64_t D, int64_t ldx, int32_t M, const float *Fold,
+                             int64_t nold, float *F, uint32_t *hist, hipStream_t s);
 // Fronts until at least `need` points are assigned, and the crowding
 // distances within them; synchronizes the stream once per front.  The same
-// in two parts: the dominator counts over all pairs, then the peeling and
-// the crowding distances.
+// in two parts: the dominator bits (hist zero before), then the fronts and the
+// crowding distances.
 hipError_t nsga_sort(const NsgaSortArgs &a, int64_t need, NsgaSortResult *res, hipStream_t s);
-hipError_t nsga_count(const NsgaSortArgs &a, hipStream_t s);
+hipError_t nsga_relate(const NsgaSortArgs &a, hipStream_t s);
 hipError_t nsga_fronts(const NsgaSortArgs &a, int64_t need, NsgaSortResult *res, hipStream_t s);
 hipError_t launch_nsga_select(const NsgaSelArgs &a, const NsgaSortResult &r, hipStream_t s);
 

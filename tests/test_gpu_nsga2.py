@@ -145,3 +145,51 @@ def test_rejects_bad_arguments(evox_gpu):
     s = ev.Swarm(ev.make_params(ev.NSGA2, 0, 8, 4, 0.0, 1.0, n_obj=3))
     with pytest.raises(ev.EvoxError):
         s.best()
+
+
+# sizes around the 64 positions of a front block, the 256 of a chunk, the 1024
+# of a chunk group and of the splitters, for every width of the padded
+# objectives; a first objective with few values (chunks that overlap), with one
+# value (no order at all), with infinities, and sorted against the others (one
+# front)
+EDGE_CASES = [("few", n, M) for n, M in ((63, 2), (65, 3), (255, 4), (257, 5), (1023, 2), (1025, 3), (2049, 8))] + \
+             [("one", 777, 3), ("one", 1300, 2), ("inf", 1500, 3), ("inf", 600, 2), ("front", 4097, 2),
+              ("front", 1025, 6), ("wide", 2600, 2), ("wide", 1999, 7)]
+
+
+@pytest.mark.parametrize("kind,n,M", EDGE_CASES)
+def test_sort_at_the_edges_of_the_coarse_order(evox_gpu, ref, kind, n, M):
+    print(f"nsga2 order {kind} n={n} M={M}", flush=True)
+    rng = np.random.default_rng(7 * n + M)
+    F = rng.random((n, M)).astype(np.float32) * 10
+    if kind == "few":
+        F[:, 0] = np.floor(F[:, 0] / 3)
+    elif kind == "one":
+        F[:, 0] = 2.5
+    elif kind == "inf":
+        F[rng.random((n, M)) < 0.1] = np.inf
+        F[:, 0][rng.random(n) < 0.1] = -np.inf
+    elif kind == "front":
+        F[:, 0] = np.arange(n)
+        F[:, 1] = -F[:, 0]
+    with np.errstate(invalid="ignore"):
+        want = ref.nds(F)
+        front, crowd = gpu_sort(evox_gpu, F)
+        assert np.array_equal(front, want)
+        if kind != "inf":  # distances of infinite ranges are not numbers
+            assert np.array_equal(crowd, ref.crowding(F, want))
+
+
+@pytest.mark.parametrize("gens", [(1, 2, 3), (4,)])
+def test_population_returns_to_the_callers_buffer(evox_gpu, ref, gens):
+    """Calls of odd and even numbers of generations: the population alternates
+    between two buffers inside a call and is in the caller's x after it."""
+    g = evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.NSGA2, 0, 130, 23, 0.0, 1.0, seed=9, n_obj=3))
+    one = evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.NSGA2, 0, 130, 23, 0.0, 1.0, seed=9, n_obj=3))
+    for n in gens:
+        g.step(n)
+        for _ in range(n):
+            one.step(1)
+        for name in ("x", "obj", "front", "crowd"):
+            assert torch.equal(getattr(g, name), getattr(one, name)), name
+        assert not g.x[:, 23:].any()
