@@ -301,8 +301,9 @@ int evox_pgpe_step(evox_state *state, int64_t n_gens);
  * min(1 - c_1, 2 (mu_eff - 2 + 1/mu_eff) / ((D + 2)^2 + mu_eff)), chi_D =
  * sqrt(D) (1 - 1/(4D) + 1/(21 D^2)).  Generation t:
  *   - deviates z_kj from Philox(seed, (floor(j/4), k, t, 9)) (the Box-Muller
- *     layout of evox_fill_normal), steps d_k = M z_k (fp32 matrix-core
- *     product), samples fma(sigma, d_kj, y_j), fit = F(samples);
+ *     layout of evox_fill_normal), steps d_k = M z_k (fp32 factors and
+ *     sums on the matrix cores, each factor as three bf16 pieces; fp32 products
+ *     where an element of M or s is outside 2^-80 .. 2^120 and not 0), samples fma(sigma, d_kj, y_j), fit = F(samples);
  *   - parents: the mu best in the argmin order;
  *   - y <- y + sigma sum w_i d_i, s <- (1 - c_s) s + sqrt(mu_eff c_s (2 - c_s))
  *     sum w_i z_i (fp64 sums, one rounding);
@@ -432,9 +433,8 @@ int evox_argsort_u32(const uint32_t *keys, int64_t N, uint32_t *perm_out, void *
  * Returns the pitch, or 0 for an unknown algo or D outside [1, EVOX_MAX_D]. */
 int64_t evox_default_ldx(int32_t algo, int64_t D);
 
-/* Dense fp32 product on the matrix cores, the contraction of the matrix-
- * adaptation ES (evox_mae_step): C = alpha op(A) op(B) + beta C with op(A)
- * M x K and op(B) K x N, row-major device matrices (op(X) = X^T when trans_x:
+/* Dense fp32 product on the matrix cores: C = alpha op(A) op(B) + beta C with
+ * op(A) M x K and op(B) K x N, row-major device matrices (op(X) = X^T when trans_x:
  * A is then stored K x M, B N x K), leading dimensions multiples of 4 and at
  * least the stored row lengths, 16-byte aligned pointers.  Accumulation in
  * fp32 (v_mfma_f32_32x32x2f32) in a fixed order, so results are reproducible;

@@ -144,10 +144,10 @@ struct Plan {
     size_t xalt = 0;          // CSO neighbourhood version: the other population buffer
     size_t mate = 0, cfit2 = 0;  // CSO: mate arrays, the other fitness buffer
     size_t esrank = 0, espart = 0;  // ES: sample ranks, gradient partial sums
-    // MA-ES: deviates, steps, split-K workspace, update factors, parents,
+    // MA-ES: deviates, their pieces, steps, split-K workspace, update factors, parents,
     // weights, path-norm partial sums
     size_t mae_z = 0, mae_d = 0, mae_work = 0, mae_at = 0, mae_bt = 0, mae_sel = 0, mae_w = 0, mae_part = 0;
-    size_t mae_wpart = 0;
+    size_t mae_wpart = 0, mae_zs = 0, mae_zs_n = 0;
     int mae_splits = 1;
     int64_t mae_mu = 0, mae_kp = 0, mae_ldf = 0;
     // NSGA-II: offspring, survivors' rows, merged objectives / fronts /
@@ -172,28 +172,22 @@ NsgaSortArgs nsga_sort_args(void *scratch, const NsgaSortScratch &l, const float
 // K-slices of the sampling product (N + 1) x D x D: a small population gives
 // few output tiles, so the product is split along K until the blocks fill
 // the chip -- a whole number of rounds of resident blocks when the occupancy
-// is known (a partial last round idles most of the chip), else about 1024
-// blocks -- with every slice at least 256 deep.
-int mae_splits(int64_t N, int64_t D, int64_t resident)
+// is known (a partial last round idles most of the chip), else about 512
+// blocks -- with every slice at least 64 deep: with slices of 256 a problem of
+// 50 x 500 ran in 4 blocks (59 us per generation, 44 in 28 blocks).
+int mae_splits(int64_t N, int64_t D)
 {
-    const int64_t rows = N + 1, bm = rows <= 64 ? 64 : rows <= 112 ? 112 : 128, bn = rows <= 128 ? 64 : 128;
-    const int64_t tiles = ((D + bn - 1) / bn) * ((rows + bm - 1) / bm);
-    int64_t sp = resident > 0 ? resident / tiles : (1024 + tiles - 1) / tiles;
-    const int64_t deep = D / 256 > 1 ? D / 256 : 1;
+    const int64_t tiles = ((D + 127) / 128) * ((N + 1 + kMaeSplitRows - 1) / kMaeSplitRows);
+    int dev = 0, cus = 0;
+    int64_t resident = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+        resident = (int64_t)cus * occupancy_mae_product();
+    int64_t sp = resident > 0 ? resident / tiles : (512 + tiles - 1) / tiles;
+    const int64_t deep = D / 64 > 1 ? D / 64 : 1;
     if (sp > deep) sp = deep;
     if (sp > 16) sp = 16;
     return (int)(sp < 1 ? 1 : sp);
-}
-
-// Blocks of the sampling product's thin tile shape resident on the device at
-// once (0 if unknown).
-int64_t resident_thin_blocks(int64_t M)
-{
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return (int64_t)cus * occupancy_gemm_nt_thin(M);
 }
 
 int make_plan(const evox_params *P, Plan *pl)
@@ -290,8 +284,10 @@ int make_plan(const evox_params *P, Plan *pl)
         const int64_t steps = (p.mae_mu + 2) / 2;
         p.mae_kp = steps <= kMaeRankUnrolled ? 2 * steps : (p.mae_mu + 1 + 31) / 32 * 32;
         p.mae_ldf = (P->D + 127) / 128 * 128;
-        p.mae_splits = mae_splits(P->N, P->D, resident_thin_blocks(P->N + 1));
+        p.mae_splits = mae_splits(P->N, P->D);
         p.mae_z = take(sizeof(float) * rows * (size_t)P->ldx);
+        p.mae_zs_n = 3 * 32 * ((D + 31) / 32) * ((rows + kMaeSplitRows - 1) / kMaeSplitRows) * kMaeSplitRows;
+        p.mae_zs = take(sizeof(uint16_t) * p.mae_zs_n);
         p.mae_d = take(sizeof(float) * rows * (size_t)P->ldx);
         p.mae_work = p.mae_splits > 1 ? take(sizeof(float) * (size_t)p.mae_splits * rows * D) : 0;
         p.mae_at = take(sizeof(float) * (size_t)p.mae_ldf * (size_t)p.mae_kp);
@@ -558,6 +554,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         MaeArgs &m = s->mae;
         m.Z = at<float>(b->scratch, pl.mae_z);
         m.Dm = at<float>(b->scratch, pl.mae_d);
+        m.Zs = at<uint16_t>(b->scratch, pl.mae_zs);
         m.N = P.N;
         m.D = P.D;
         m.ldx = P.ldx;
@@ -685,6 +682,8 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
             ((e = launch_fill(b->v, P.ldx, 0.0f, s->stream)) != hipSuccess ||
              (e = launch_mae_identity(b->mat, P.D, P.ldx, s->stream)) != hipSuccess ||
              (e = launch_fill(s->mae.At, s->mae.kp * s->mae.ldf, 0.0f, s->stream)) != hipSuccess ||
+             (e = launch_zero_u32(reinterpret_cast<uint32_t *>(s->mae.Zs), (int64_t)pl.mae_zs_n / 2, s->stream)) !=
+                 hipSuccess ||
              (e = launch_fill(s->mae.Bt, s->mae.kp * s->mae.ldf, 0.0f, s->stream)) != hipSuccess ||
              (e = launch_fill(b->sigma, 1, P.es_sigma, s->stream)) != hipSuccess ||
              (e = hipMemcpyAsync((void *)s->mae.w, s->mae_w.data(), sizeof(double) * s->mae_w.size(),
@@ -1082,16 +1081,13 @@ int mae_generations(evox_state *s, int64_t n_gens)
     const evox_params &P = s->P;
     const Plan &pl = s->pl;
     MaeArgs m = s->mae;
-    // the sampling product Dm = Z M^T ((N + 1) x D over K = D); the update
-    // M <- beta M + At^T Bt is the rank pass
-    const GemmArgs sample{P.N + 1, P.D, P.D, 1.0f, m.Z, P.ldx, s->B.mat, P.ldx, 0.0f, m.Dm, P.ldx};
     hipError_t e;
     for (int64_t k = 0; k < n_gens; ++k) {
         m.t = (uint32_t)(s->t + k);
         MaeEvalArgs ea{s->B.x, m.Dm, P.ldx, s->B.sigma, s->B.fit, s->esrank, P.N, P.D,
                        k == n_gens - 1 ? s->slots : nullptr};
         if ((e = launch_mae_sample(m, s->stream)) != hipSuccess) return hip_fail(e, "deviates");
-        if ((e = timed(s, [&] { return launch_gemm_nt(sample, pl.mae_splits, s->mae_work, s->stream); })) !=
+        if ((e = timed(s, [&] { return launch_mae_product(m, s->B.mat, pl.mae_splits, s->mae_work, s->stream); })) !=
             hipSuccess)
             return hip_fail(e, "sampling product");
         if ((e = launch_mae_eval(P.fn_id, pl.L, ea, pl.grid, s->stream)) != hipSuccess)

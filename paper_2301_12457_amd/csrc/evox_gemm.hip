@@ -123,20 +123,14 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 }
 
 // ---------------------------------------------------------------------------
-// C = alpha A B^T + beta C with A [M x K] and B [N x K] both K-contiguous, the
-// layout of the two contractions of the matrix-adaptation ES (samples times
-// M^T, and the rank-mu update).  Block tile BM x BN (BM, BN in {64, 128}),
-// 2 x 2 waves of (BM/2) x (BN/2), each a grid of 32x32x2 MFMA accumulators;
+// C = alpha A B^T + beta C with A [M x K] and B [N x K] both K-contiguous.
+// Block tile BM x BN (BM, BN in {64, 128}), 2 x 2 waves of (BM/2) x (BN/2), each a grid of 32x32x2 MFMA accumulators;
 // K in tiles of 32, each staged in LDS row-major ([row][k], rows padded to 36
 // floats so that every row starts 16-byte aligned) after being prefetched
 // into registers while the previous tile is multiplied.  Within a tile, lane
 // half h = l / 32 takes k = 16 h + step (steps 0..15), so each lane reads its
 // operands as float4 runs along k; the order in which the products are summed
 // is fixed.
-// Split-K (gridDim.z = splits): block z sums k in [z kc, (z + 1) kc) and, with
-// a workspace, stores its raw partial tile there; k_splitk_reduce then adds
-// the partials in order z = 0, 1, ... and applies alpha and beta.  Without a
-// workspace (one split) the block applies alpha and beta itself.
 // ---------------------------------------------------------------------------
 constexpr int kNtBK = 32, kNtLD = kNtBK + 4;
 // register stages of the operand prefetch for the thin tiles (M <= 128,
@@ -144,7 +138,7 @@ constexpr int kNtBK = 32, kNtLD = kNtBK + 4;
 constexpr int kNtThinDepth = 2;
 
 template <int BM, int BN, int DEPTH>
-__global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g, float *work, int64_t kc)
+__global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g)
 {
     constexpr int TM = BM / 64, TN = BN / 64;            // 32x32 tiles per wave
     constexpr int QA = BM * kNtBK / 4 / 256, QB = BN * kNtBK / 4 / 256;  // float4 per thread
@@ -153,7 +147,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g, float *work, int64_
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, col = lane % 32, h = lane / 32;
     const int wm = wave / 2, wn = wave % 2;
     const int64_t i0 = (int64_t)blockIdx.y * BM, j0 = (int64_t)blockIdx.x * BN;
-    const int64_t kb = (int64_t)blockIdx.z * kc, ke = kb + kc < g.K ? kb + kc : g.K;
+    const int64_t kb = 0, ke = g.K;
     // DEPTH register stages of the next K tiles' operands (compile-time
     // stage indices, so they stay in registers)
     float4 ra[DEPTH][QA], rb[DEPTH][QB];
@@ -242,17 +236,13 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g, float *work, int64_
                 const int64_t i = i0 + wm * TM * 32 + m * 32 + (v / 4) * 8 + h * 4 + v % 4;
                 const int64_t j = j0 + wn * TN * 32 + n * 32 + col;
                 if (i < g.M && j < g.N) {
-                    if (work) {
-                        work[((int64_t)blockIdx.z * g.M + i) * g.N + j] = acc[m][n][v];
-                    } else {
-                        float *c = g.C + i * g.ldc + j;
-                        *c = g.beta != 0.0f ? fmaf(g.alpha, acc[m][n][v], g.beta * *c) : g.alpha * acc[m][n][v];
-                    }
+                    float *c = g.C + i * g.ldc + j;
+                    *c = g.beta != 0.0f ? fmaf(g.alpha, acc[m][n][v], g.beta * *c) : g.alpha * acc[m][n][v];
                 }
             }
 }
 
-// A B^T for at most 16 RB rows of A (the thin sampling products): 16 x 16
+// A B^T for at most 16 RB rows of A: 16 x 16
 // MFMA tiles (v_mfma_f32_16x16x4f32), so 101 rows pad to 112 instead of
 // 128.  Block: all 16 RB rows x 64 columns, K tile kNtBK; wave w owns the
 // 16-column block w and the RB row blocks.  Within a K tile, lane group
@@ -261,7 +251,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g, float *work, int64_
 // product, since A and B use the same one), so each lane reads its
 // operands as two float4 per row block.  Operand prefetch as in k_gemm_nt.
 template <int RB, int DEPTH>
-__global__ __launch_bounds__(256) void k_gemm_nt16(GemmArgs g, float *work, int64_t kc)
+__global__ __launch_bounds__(256) void k_gemm_nt16(GemmArgs g)
 {
     constexpr int BM = 16 * RB, BN = 64;
     constexpr int FA = BM * kNtBK / 4, FB = BN * kNtBK / 4;  // float4 per tile
@@ -270,7 +260,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt16(GemmArgs g, float *work, int6
     __shared__ float Bs[BN * kNtLD];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, r16 = lane % 16, q = lane / 16;
     const int64_t i0 = (int64_t)blockIdx.y * BM, j0 = (int64_t)blockIdx.x * BN;
-    const int64_t kb = (int64_t)blockIdx.z * kc, ke = kb + kc < g.K ? kb + kc : g.K;
+    const int64_t kb = 0, ke = g.K;
     float4 ra[DEPTH][QA], rb[DEPTH][QB];
     auto load = [&](int d, int64_t k0) {
 #pragma unroll
@@ -343,16 +333,13 @@ __global__ __launch_bounds__(256) void k_gemm_nt16(GemmArgs g, float *work, int6
         for (int v = 0; v < 4; ++v) {
             const int64_t i = i0 + m * 16 + 4 * q + v, j = j0 + wave * 16 + r16;
             if (i < g.M && j < g.N) {
-                if (work) {
-                    work[((int64_t)blockIdx.z * g.M + i) * g.N + j] = acc[m][v];
-                } else {
-                    float *c = g.C + i * g.ldc + j;
-                    *c = g.beta != 0.0f ? fmaf(g.alpha, acc[m][v], g.beta * *c) : g.alpha * acc[m][v];
-                }
+                float *c = g.C + i * g.ldc + j;
+                *c = g.beta != 0.0f ? fmaf(g.alpha, acc[m][v], g.beta * *c) : g.alpha * acc[m][v];
             }
         }
 }
 
+// C = alpha (partials added in order z = 0, 1, ...) + beta C.
 __global__ __launch_bounds__(256) void k_splitk_reduce(GemmArgs g, const float *work, int splits)
 {
     const int64_t n = g.M * g.N;
@@ -367,47 +354,32 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(GemmArgs g, const float *
 
 }  // namespace
 
-int occupancy_gemm_nt_thin(int64_t M)
-{
-    int n = 0;
-    const hipError_t e = M > 64 && M <= 112
-                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gemm_nt16<7, kNtThinDepth>, 256, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gemm_nt<128, 64, kNtThinDepth>, 256, 0);
-    return e == hipSuccess ? n : 0;
-}
-
-int64_t gemm_nt_chunk(int64_t K, int splits)
-{
-    const int64_t per = (K + splits - 1) / splits;
-    return (per + kNtBK - 1) / kNtBK * kNtBK;
-}
-
-hipError_t launch_gemm_nt(const GemmArgs &g, int splits, float *work, hipStream_t s)
+hipError_t launch_gemm_nt(const GemmArgs &g, hipStream_t s)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (splits < 1 || (splits > 1 && !work)) return hipErrorInvalidValue;
-    const int64_t kc = splits > 1 ? gemm_nt_chunk(g.K, splits) : (g.K > 0 ? g.K : 1);
     // 65..112 rows: 16 x 16 tiles (7 row blocks) instead of 128 padded rows
     const bool rows112 = g.M > 64 && g.M <= 112;
     const int bm = g.M <= 64 ? 64 : rows112 ? 112 : 128, bn = g.M <= 128 ? 64 : 128;
-    const dim3 grid((unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm), (unsigned)splits);
-    float *w = splits > 1 ? work : nullptr;
-    if (rows112) hipLaunchKernelGGL((k_gemm_nt16<7, kNtThinDepth>), grid, dim3(256), 0, s, g, w, kc);
-    else if (bm == 64) hipLaunchKernelGGL((k_gemm_nt<64, 64, kNtThinDepth>), grid, dim3(256), 0, s, g, w, kc);
-    else if (bn == 64) hipLaunchKernelGGL((k_gemm_nt<128, 64, kNtThinDepth>), grid, dim3(256), 0, s, g, w, kc);
-    else hipLaunchKernelGGL((k_gemm_nt<128, 128, 1>), grid, dim3(256), 0, s, g, w, kc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
+    const dim3 grid((unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm));
+    if (rows112) hipLaunchKernelGGL((k_gemm_nt16<7, kNtThinDepth>), grid, dim3(256), 0, s, g);
+    else if (bm == 64) hipLaunchKernelGGL((k_gemm_nt<64, 64, kNtThinDepth>), grid, dim3(256), 0, s, g);
+    else if (bn == 64) hipLaunchKernelGGL((k_gemm_nt<128, 64, kNtThinDepth>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm_nt<128, 128, 1>), grid, dim3(256), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_splitk_reduce(const GemmArgs &g, int splits, const float *work, hipStream_t s)
+{
     const int64_t n = g.M * g.N, blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, g,
-                       (const float *)work, splits);
+    hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, g, work,
+                       splits);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm(bool ta, bool tb, const GemmArgs &g, hipStream_t s)
 {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    if (!ta && tb) return launch_gemm_nt(g, 1, nullptr, s);
+    if (!ta && tb) return launch_gemm_nt(g, s);
     const dim3 grid((unsigned)((g.N + kBN - 1) / kBN), (unsigned)((g.M + kBM - 1) / kBM));
     if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(256), 0, s, g);
     if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(256), 0, s, g);

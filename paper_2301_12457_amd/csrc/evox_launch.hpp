@@ -84,8 +84,10 @@ struct MaeEvalArgs {
     int64_t N, D;
     SelSlots *slots;      // nullable
 };
+constexpr int kMaeSplitRows = 112;    // rows per tile of the split deviates
 struct MaeArgs {
     float *Z, *Dm;        // [(N + 1)][ldx]
+    uint16_t *Zs;         // [row tiles][ceil(D / 32)][3][4][112][8] the bf16 pieces of Z, zero past row N and column D
     int64_t N, D, ldx, mu;
     int64_t kp, ldf;      // factor terms (mu + 1 padded with zero terms) and their pitch
     const uint32_t *rank; // [N]
@@ -99,11 +101,13 @@ struct MaeArgs {
     uint32_t k0, k1, t;
 };
 hipError_t launch_mae_sample(const MaeArgs &a, hipStream_t s);
+// Dm = Z M^T with `splits` K-slices (splits > 1: work of splits (N + 1) D floats).
+hipError_t launch_mae_product(const MaeArgs &a, const float *M, int splits, float *work, hipStream_t s);
+int occupancy_mae_product();  // its resident blocks per CU
 hipError_t launch_mae_select(const MaeArgs &a, hipStream_t s);
 hipError_t launch_mae_recombine(const MaeArgs &a, hipStream_t s);  // and the step size
 hipError_t launch_mae_rank(const MaeArgs &a, float *M, float beta, hipStream_t s);  // M <- beta M + At^T Bt
 hipError_t launch_mae_identity(float *M, int64_t D, int64_t ldx, hipStream_t s);
-int occupancy_gemm_nt_thin(int64_t M);  // resident blocks per CU of the tile shape for M rows (M <= 128)
 
 // NSGA-II on DTLZ1.
 constexpr int kNsgaMaxM = 8;          // objectives
@@ -194,11 +198,9 @@ struct GemmArgs {
     int64_t ldc;
 };
 hipError_t launch_gemm(bool ta, bool tb, const GemmArgs &g, hipStream_t s);
-// The A B^T product (A [M x K], B [N x K]) with `splits` K-slices; splits > 1
-// needs a workspace of splits * M * N floats.  gemm_nt_chunk: the K extent of
-// one slice.
-hipError_t launch_gemm_nt(const GemmArgs &g, int splits, float *work, hipStream_t s);
-int64_t gemm_nt_chunk(int64_t K, int splits);
+hipError_t launch_gemm_nt(const GemmArgs &g, hipStream_t s);  // the A B^T product (A [M x K], B [N x K])
+// C = alpha (the sum of `splits` partial products work [splits][M][N], in order) + beta C.
+hipError_t launch_splitk_reduce(const GemmArgs &g, int splits, const float *work, hipStream_t s);
 
 struct EvalArgs {
     const float *X;

@@ -18,11 +18,82 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// ---------------------------------------------------------------------------
+// The sampling product Dm = Z M^T on the bf16 matrix cores, in fp32 precision.
+// Each operand is the exact sum of three bf16 numbers, x = h + m + l (each the
+// rounding of what the ones before leave: 8 + 8 + 8 bits), and of the nine
+// products of pieces the six down to 2^-18 are summed in fp32; the three left
+// out are below 2^-25 of the term, less than the rounding of one fp32 product.
+// Six bf16 products cost 6 / 16 of one fp32 product on gfx950 (2.5 PFLOP/s
+// against 157 TFLOP/s).
+//
+// That holds for magnitudes whose pieces neither overflow nor fall below the
+// normal numbers: kSplitLo <= |x| < kSplitHi, or 0.  A block that meets another
+// element, of M or of the path s (a deviate is 0 or within 2^-40 .. 2^3), computes
+// its tile again with fp32 products (v_mfma_f32_16x16x4f32), so that infinities
+// and tiny numbers come out as they would without the split; a NaN stays one in
+// either product.
+//
+// Z is split where it is drawn, into tiles of 3 pieces x 4 groups of 8 columns x
+// 112 rows that a block copies to LDS as they are (16 lanes of one column group
+// read 256 consecutive bytes); M is read from memory straight into
+// the operand registers -- lane l holds 8 consecutive k of row l % 16, a whole
+// 128-byte line per row -- and split there, so it passes through no LDS and is
+// split once per row tile.  Block: 112 rows x 128 columns, 4 waves of 112 x 32
+// (7 x 2 tiles of v_mfma_f32_16x16x32_bf16, 84 per 32 columns of K).
+//
+// At 101 x 16384 x 16384: 380 us (the fp32 matrix-core product of before took 560
+// in k_gemm_nt16 and its split-K reduction), against 167 us for one pass over M at
+// the copy rate, 148 us of matrix-core cycles at 2.4 GHz and 306 us at the rate a
+// large bf16 library product reaches here; what is left is M's latency with two
+// waves per SIMD.  A generation: 1002 -> 789 us; 4096 x 1830: 553 -> 487; 700 x
+// 6000: 1156 -> 827; 50 x 500: 52 -> 48.  Pieces stored row by row ([112][32])
+// cost 22M bank conflicts and 12 us; operand arrays of HIP's class vectors went to
+// scratch (660 us); a loop exit between the steps of a group made every load of
+// M wait at once (+11 us).
+// Error against 64 bits, relative rms over the steps, before and now: D = 100
+// 1.8e-7, 1.4e-7; 500 4.0e-7, 1.4e-7; 4096 3.4e-7, 2.5e-7; 8192 6.6e-7, 5.1e-7
+// (one fp32 rounding per 32 columns and product of pieces, not per column pair);
+// below D = 3, where one product's own rounding shows, the fp32 path is taken.
+// ---------------------------------------------------------------------------
+constexpr int kSpRows = kMaeSplitRows, kSpCols = 128, kSpRB = kSpRows / 16;
+constexpr int kSpTile = 3 * kSpRows * 32;  // bf16 numbers of one tile of Z
+constexpr uint32_t kSplitLo = (127 - 80) << 23, kSplitHi = (127 + 120) << 23;  // 2^-80, 2^120
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The two numbers rounded to bf16, packed.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    const bf16x2 t = __builtin_convertvector((f32x2){a, b}, bf16x2);
+    return __builtin_bit_cast(uint32_t, t);
+}
+
+// The three pieces of a pair of numbers, packed.
+__device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    h = pack_bf16(a, b);
+    const float a1 = a - __uint_as_float(h << 16), b1 = b - __uint_as_float(h & 0xffff0000u);
+    m = pack_bf16(a1, b1);
+    l = pack_bf16(a1 - __uint_as_float(m << 16), b1 - __uint_as_float(m & 0xffff0000u));
+}
+
+// Whether x cannot be split: not 0 and outside [2^-80, 2^120).
+__device__ __forceinline__ bool odd_number(float x)
+{
+    const uint32_t e = __float_as_uint(x) & 0x7fffffffu;
+    return e != 0 && (e < kSplitLo || e >= kSplitHi);
+}
+
 // Deviates z_k (rows k < N, Philox stream 9 with the generation in the
-// counter) and the path s (row N); columns D..ldx-1 zero.
+// counter) and the path s (row N); columns D..ldx-1 zero.  Also their pieces.
 __global__ __launch_bounds__(256) void k_mae_sample(MaeArgs a)
 {
-    const int64_t q4 = a.ldx / 4, total = (a.N + 1) * q4;
+    const int64_t q4 = a.ldx / 4, total = (a.N + 1) * q4, kb = (a.D + 31) / 32;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < total; q += (int64_t)gridDim.x * 256) {
         const int64_t row = q / q4, c = q % q4;
         float4 v;
@@ -34,9 +105,212 @@ __global__ __launch_bounds__(256) void k_mae_sample(MaeArgs a)
             v.w = 4 * c + 3 < a.D ? z.w : 0.0f;
         } else {
             v = *reinterpret_cast<const float4 *>(a.s + 4 * c);
+            v.x = 4 * c + 0 < a.D ? v.x : 0.0f;
+            v.y = 4 * c + 1 < a.D ? v.y : 0.0f;
+            v.z = 4 * c + 2 < a.D ? v.z : 0.0f;
+            v.w = 4 * c + 3 < a.D ? v.w : 0.0f;
         }
         *reinterpret_cast<float4 *>(a.Z + row * a.ldx + 4 * c) = v;
+        if (4 * c >= 32 * kb) continue;  // padding past the last tile
+        uint32_t p[3][2];
+        split2(v.x, v.y, p[0][0], p[1][0], p[2][0]);
+        split2(v.z, v.w, p[0][1], p[1][1], p[2][1]);
+        uint16_t *dst = a.Zs + ((row / kSpRows) * kb + c / 8) * kSpTile +
+                        ((c % 8) / 2 * kSpRows + row % kSpRows) * 8 + 4 * (c % 2);
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            *reinterpret_cast<uint2 *>(dst + u * kSpRows * 32) = make_uint2(p[u][0], p[u][1]);
     }
+}
+
+// K in steps of 32; the steps [s0, s1) of split z = blockIdx.x % splits.  With
+// several splits the partial tile goes to work[z]; k_splitk_reduce adds them in
+// order.  Operands in flight: M's next kSpDepth steps in registers, Z's next
+// tile in registers and the one after that in the other LDS buffer.
+constexpr int kSpDepth = 3;
+
+__global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *M, int splits, float *work)
+{
+    __shared__ __align__(16) uint16_t As[2][kSpTile];
+    __shared__ int32_t odd;
+    constexpr int NA = kSpTile / 8, QA = (NA + 255) / 256;  // 16-byte pieces of a tile, per thread
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kg = lane >> 4;
+    const int z = blockIdx.x % splits;
+    const int64_t tn = (a.D + kSpCols - 1) / kSpCols, tile = blockIdx.x / splits;
+    const int64_t rt = tile / tn, j0 = tile % tn * kSpCols + 32 * wave;
+    const int steps = (int)((a.D + 31) / 32), per = (steps + splits - 1) / splits;
+    const int s0 = z * per, s1 = s0 + per < steps ? s0 + per : steps;
+    const int64_t rows = a.N + 1, i0 = rt * kSpRows;
+    const u32x4 *At = reinterpret_cast<const u32x4 *>(a.Zs) + rt * steps * NA;
+
+    // the lane's two rows of M (past the last row the last one, for columns that
+    // are not stored; k past the last column is read from inside and zeroed)
+    const float *mrow[2];
+    bool in[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int64_t j = j0 + 16 * n + r16;
+        in[n] = j < a.D;
+        mrow[n] = M + (in[n] ? j : a.D - 1) * a.ldx;
+    }
+    f32x4 bq[kSpDepth][2][2];
+    auto load_b = [&](f32x4 (&b)[2][2], int s) {
+        const int64_t k = 32 * (int64_t)s + 8 * kg;
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                b[n][h] = *reinterpret_cast<const f32x4 *>(mrow[n] + (k + 4 * h < a.ldx ? k + 4 * h : 0));
+    };
+    u32x4 aq[QA];
+    auto load_a = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < QA; ++u) {
+            const int e = tid + 256 * u;  // the last round's spare threads copy the last piece again
+            aq[u] = At[(int64_t)s * NA + (e < NA ? e : NA - 1)];
+        }
+    };
+    auto store_a = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < QA; ++u) {
+            const int e = tid + 256 * u;
+            reinterpret_cast<u32x4 *>(As[buf])[e < NA ? e : NA - 1] = aq[u];
+        }
+    };
+    auto lds_barrier = [] {  // fences LDS only: loads stay in flight
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    f32x4 acc[kSpRB][2];
+#pragma unroll
+    for (int m = 0; m < kSpRB; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) acc[m][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // the range of M's elements: greatest magnitude (NaN aside: it comes out of
+    // either product), least bits of a magnitude other than 0, times 2, less 1
+    float big = 0.0f;
+    uint32_t small = 0xffffffffu;
+    bool sodd = false;  // an element of the path in this slice cannot be split
+    if (rows - i0 <= kSpRows)
+        for (int64_t k = 32 * (int64_t)s0 + tid; k < 32 * (int64_t)s1 && k < a.D; k += 256)
+            sodd = sodd || odd_number(a.s[k]);
+    if (tid == 0) odd = a.D <= 2;
+
+    if (s0 < s1) {
+        const int last = s1 - 1;
+        load_a(s0);
+#pragma unroll
+        for (int d = 0; d < kSpDepth; ++d) load_b(bq[d], s0 + d < last ? s0 + d : last);
+        store_a(0);
+        load_a(s0 + 1 < last ? s0 + 1 : last);
+        lds_barrier();
+        for (int sb = s0; sb < s1; sb += kSpDepth) {
+#pragma unroll
+            for (int d = 0; d < kSpDepth; ++d) {
+                // a last group's steps past s1 run on zeros: no branch leaves the
+                // group, so every load is waited for by its own count
+                const int s = sb + d, buf = (s - s0) & 1;
+                store_a(buf ^ 1);
+                load_a(s + 2 < last ? s + 2 : last);
+                __builtin_amdgcn_sched_barrier(0);  // the loads keep this order, oldest needed first
+                const int64_t k = 32 * (int64_t)s + 8 * kg;
+                if (s >= s1 - 1) {  // the last step may pass the last column
+#pragma unroll
+                    for (int n = 0; n < 2; ++n)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                bq[d][n][h][e] = s < s1 && k + 4 * h + e < a.D ? bq[d][n][h][e] : 0.0f;
+                }
+                // M's elements of this step: range, pieces
+                uint32_t hp[2][4], mp[2][4], lp[2][4];
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const f32x4 v = bq[d][n][h];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            big = fmaxf(big, fabsf(v[e]));
+                            const uint32_t t = (__float_as_uint(v[e]) << 1) - 1u;  // 0: the greatest
+                            small = t < small ? t : small;
+                        }
+                        split2(v[0], v[1], hp[n][2 * h], mp[n][2 * h], lp[n][2 * h]);
+                        split2(v[2], v[3], hp[n][2 * h + 1], mp[n][2 * h + 1], lp[n][2 * h + 1]);
+                    }
+                load_b(bq[d], s + kSpDepth < last ? s + kSpDepth : last);
+                __builtin_amdgcn_sched_barrier(0);
+                bf16x8 bh[2], bm[2], bl[2];
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    bh[n] = __builtin_bit_cast(bf16x8, (u32x4){hp[n][0], hp[n][1], hp[n][2], hp[n][3]});
+                    bm[n] = __builtin_bit_cast(bf16x8, (u32x4){mp[n][0], mp[n][1], mp[n][2], mp[n][3]});
+                    bl[n] = __builtin_bit_cast(bf16x8, (u32x4){lp[n][0], lp[n][1], lp[n][2], lp[n][3]});
+                }
+                const uint16_t *src = As[buf] + (kg * kSpRows + r16) * 8;
+#pragma unroll
+                for (int m = 0; m < kSpRB; ++m) {
+                    const bf16x8 ah = *reinterpret_cast<const bf16x8 *>(src + m * 16 * 8);
+                    const bf16x8 am = *reinterpret_cast<const bf16x8 *>(src + kSpRows * 32 + m * 16 * 8);
+                    const bf16x8 al = *reinterpret_cast<const bf16x8 *>(src + 2 * kSpRows * 32 + m * 16 * 8);
+                    // small terms first
+#define EVOX_TERM(X, Y)                                                                                      \
+    _Pragma("unroll") for (int n = 0; n < 2; ++n) acc[m][n] =                                                \
+        __builtin_amdgcn_mfma_f32_16x16x32_bf16(X, Y[n], acc[m][n], 0, 0, 0)
+                    EVOX_TERM(al, bh);
+                    EVOX_TERM(ah, bl);
+                    EVOX_TERM(am, bm);
+                    EVOX_TERM(am, bh);
+                    EVOX_TERM(ah, bm);
+                    EVOX_TERM(ah, bh);
+#undef EVOX_TERM
+                }
+                lds_barrier();
+            }
+        }
+    }
+    // the loop's barriers order this after the first value; every writer stores 1
+    if (sodd || big >= __uint_as_float(kSplitHi) || small < 2u * kSplitLo - 1u) odd = 1;
+    __syncthreads();
+    if (odd) {
+        // fp32 products: lane l holds k 4 u + kg of row r16, u = 0 .. 7
+#pragma unroll
+        for (int m = 0; m < kSpRB; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) acc[m][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int s = s0; s < s1; ++s)
+            for (int u = 0; u < 8; ++u) {
+                const int64_t k = 32 * (int64_t)s + 4 * u + kg;
+                float bv[2];
+#pragma unroll
+                for (int n = 0; n < 2; ++n) bv[n] = in[n] && k < a.D ? mrow[n][k] : 0.0f;
+#pragma unroll
+                for (int m = 0; m < kSpRB; ++m) {
+                    const int64_t i = i0 + 16 * m + r16;
+                    const float av = i < rows && k < a.D ? a.Z[i * a.ldx + k] : 0.0f;
+#pragma unroll
+                    for (int n = 0; n < 2; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[n], acc[m][n], 0, 0, 0);
+                }
+            }
+    }
+    // result v of tile (m, n): row 16 m + 4 kg + v, column 16 n + r16
+#pragma unroll
+    for (int m = 0; m < kSpRB; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t i = i0 + 16 * m + 4 * kg + v, j = j0 + 16 * n + r16;
+                if (i < rows && j < a.D) {
+                    if (splits > 1)
+                        work[((int64_t)z * rows + i) * a.D + j] = acc[m][n][v];
+                    else
+                        a.Dm[i * a.ldx + j] = acc[m][n][v];
+                }
+            }
 }
 
 // sel[r] = the sample of rank r, for the mu best.
@@ -323,6 +597,23 @@ hipError_t launch_mae_sample(const MaeArgs &a, hipStream_t s)
 {
     hipLaunchKernelGGL(k_mae_sample, dim3(blocks_for((a.N + 1) * (a.ldx / 4), 256, 16384)), dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+int occupancy_mae_product()
+{
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_mae_product, 256, 0) == hipSuccess ? n : 0;
+}
+
+hipError_t launch_mae_product(const MaeArgs &a, const float *M, int splits, float *work, hipStream_t s)
+{
+    if (splits < 1 || (splits > 1 && !work)) return hipErrorInvalidValue;
+    const int64_t tiles = ((a.D + kSpCols - 1) / kSpCols) * ((a.N + 1 + kSpRows - 1) / kSpRows);
+    hipLaunchKernelGGL(k_mae_product, dim3((unsigned)(tiles * splits)), dim3(256), 0, s, a, M, splits, work);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    return launch_splitk_reduce(GemmArgs{a.N + 1, a.D, a.D, 1.0f, nullptr, 0, nullptr, 0, 0.0f, a.Dm, a.ldx}, splits,
+                                work, s);
 }
 
 hipError_t launch_mae_select(const MaeArgs &a, hipStream_t s)

@@ -170,6 +170,61 @@ def test_lockstep_generations(evox_gpu, ref, case):
     assert compared >= 1
 
 
+# The sampling product's tiles are 112 rows (samples and the path) by 128
+# columns, K in steps of 32 and slices of at least 64.
+@pytest.mark.parametrize("N, D", [(111, 31), (112, 32), (110, 33), (5, 63), (223, 127), (224, 128), (40, 129),
+                                  (30, 161), (12, 383)])
+def test_dense_matrix_at_tile_edges(evox_gpu, ref, N, D):
+    print(f"maes dense M {N} x {D}", flush=True)
+    rng = np.random.default_rng(100 * N + D)
+    g, r = pair(evox_gpu, ref, SPHERE, N, D, 3, -5.0, 5.0, 0.4)
+    r.M[:] = rng.standard_normal((D, D)) / np.sqrt(D) * 2.0 ** rng.integers(-8, 9, (D, D))
+    r.s[:] = rng.standard_normal(D)
+    lockstep(evox_gpu, ref, g, r, SPHERE, f"{N} x {D}")
+
+
+# Elements that three bf16 pieces cannot hold, in all of M, in one row of it or
+# in the path only: sigma brings the samples back to about 1.
+@pytest.mark.parametrize("scale, where", [(-90, "M"), (-110, "row"), (121, "M"), (122, "row"), (-100, "path"),
+                                          (-140, "path"), (121, "path")])
+def test_elements_outside_the_split_range(evox_gpu, ref, scale, where):
+    print(f"maes 2^{scale} in {where}", flush=True)
+    N, D = 20, 70
+    rng = np.random.default_rng(5)
+    g, r = pair(evox_gpu, ref, SPHERE, N, D, 3, -5.0, 5.0, 0.4)
+    r.M[:] = rng.standard_normal((D, D)) / 16
+    if where == "path":
+        r.s[:] = (rng.standard_normal(D) * 2.0 ** scale).astype(np.float32)
+        if scale > 0:  # the step size cannot follow such a path: look at the samples only
+            push(g, r)
+            g.step(1)
+            z = ref.maes_deviates(3, 0, N, D).astype(np.float64)
+            X = r.y + 0.4 * (z @ r.M.astype(np.float64).T)
+            np.testing.assert_allclose(g.fit.cpu().numpy(), (X * X).sum(1), rtol=1e-4)
+            return
+    else:
+        sel = slice(None) if where == "M" else slice(66, 67)
+        r.M[sel] = r.M[sel] * np.float32(2.0 ** scale)
+        if where == "M":
+            r.y[:] = 0.0 if scale > 0 else r.y
+            r.sigma[:] = 2.0 ** -scale
+    if where == "row" and scale > 0:
+        r.sigma[:] = 2.0 ** -60  # one coordinate of about 2^62: its square is finite in fp32
+    lockstep(evox_gpu, ref, g, r, SPHERE, f"2^{scale} in {where}")
+
+
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+def test_non_finite_matrix_element(evox_gpu, ref, value):
+    N, D, i, j = 9, 150, 140, 7
+    g, r = pair(evox_gpu, ref, SPHERE, N, D, 3, -5.0, 5.0, 0.4)
+    r.M[i, j] = value
+    push(g, r)
+    g.step(1)
+    fit, x = g.fit.cpu().numpy(), g.x[:D].cpu().numpy()
+    assert np.all(np.isnan(fit)) if math.isnan(value) else np.all(fit == math.inf)
+    assert not np.isfinite(x[i]) and np.all(np.isfinite(np.delete(x, i)))
+
+
 def test_initial_state(evox_gpu, ref):
     g, r = pair(evox_gpu, ref, SPHERE, 10, 37, 5, -5.0, 5.0, 0.7)
     D = 37
