@@ -177,12 +177,13 @@ NsgaSortArgs nsga_sort_args(void *scratch, const NsgaSortScratch &l, const float
 // 50 x 500 ran in 4 blocks (59 us per generation, 44 in 28 blocks).
 int mae_splits(int64_t N, int64_t D)
 {
-    const int64_t tiles = ((D + 127) / 128) * ((N + 1 + kMaeSplitRows - 1) / kMaeSplitRows);
+    const int zr = mae_tile_rows(N + 1);
+    const int64_t tiles = ((D + 127) / 128) * ((N + zr) / zr);
     int dev = 0, cus = 0;
     int64_t resident = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-        resident = (int64_t)cus * occupancy_mae_product();
+        resident = (int64_t)cus * occupancy_mae_product(zr);
     int64_t sp = resident > 0 ? resident / tiles : (512 + tiles - 1) / tiles;
     const int64_t deep = D / 64 > 1 ? D / 64 : 1;
     if (sp > deep) sp = deep;
@@ -286,7 +287,8 @@ int make_plan(const evox_params *P, Plan *pl)
         p.mae_ldf = (P->D + 127) / 128 * 128;
         p.mae_splits = mae_splits(P->N, P->D);
         p.mae_z = take(sizeof(float) * rows * (size_t)P->ldx);
-        p.mae_zs_n = 3 * 32 * ((D + 31) / 32) * ((rows + kMaeSplitRows - 1) / kMaeSplitRows) * kMaeSplitRows;
+        const size_t zr = (size_t)mae_tile_rows(P->N + 1);
+        p.mae_zs_n = 3 * 32 * ((D + 31) / 32) * ((rows + zr - 1) / zr) * zr;
         p.mae_zs = take(sizeof(uint16_t) * p.mae_zs_n);
         p.mae_d = take(sizeof(float) * rows * (size_t)P->ldx);
         p.mae_work = p.mae_splits > 1 ? take(sizeof(float) * (size_t)p.mae_splits * rows * D) : 0;
@@ -555,6 +557,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         m.Z = at<float>(b->scratch, pl.mae_z);
         m.Dm = at<float>(b->scratch, pl.mae_d);
         m.Zs = at<uint16_t>(b->scratch, pl.mae_zs);
+        m.zr = mae_tile_rows(P.N + 1);
         m.N = P.N;
         m.D = P.D;
         m.ldx = P.ldx;

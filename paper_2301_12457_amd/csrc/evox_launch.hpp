@@ -84,10 +84,17 @@ struct MaeEvalArgs {
     int64_t N, D;
     SelSlots *slots;      // nullable
 };
-constexpr int kMaeSplitRows = 112;    // rows per tile of the split deviates
+// Rows per tile of the split deviates: the fewest of the compiled shapes that
+// hold all rows, 112 per tile for more of them, but for 113 .. 128 rows, of which
+// two tiles of 112 would be half padding.
+inline int mae_tile_rows(int64_t rows)
+{
+    return rows <= 32 ? 32 : rows <= 64 || (rows > 112 && rows <= 128) ? 64 : 112;
+}
 struct MaeArgs {
     float *Z, *Dm;        // [(N + 1)][ldx]
-    uint16_t *Zs;         // [row tiles][ceil(D / 32)][3][4][112][8] the bf16 pieces of Z, zero past row N and column D
+    uint16_t *Zs;         // [row tiles][ceil(D / 32)][3][4][zr][8] the bf16 pieces of Z, zero past row N and column D
+    int32_t zr;           // mae_tile_rows(N + 1)
     int64_t N, D, ldx, mu;
     int64_t kp, ldf;      // factor terms (mu + 1 padded with zero terms) and their pitch
     const uint32_t *rank; // [N]
@@ -103,7 +110,7 @@ struct MaeArgs {
 hipError_t launch_mae_sample(const MaeArgs &a, hipStream_t s);
 // Dm = Z M^T with `splits` K-slices (splits > 1: work of splits (N + 1) D floats).
 hipError_t launch_mae_product(const MaeArgs &a, const float *M, int splits, float *work, hipStream_t s);
-int occupancy_mae_product();  // its resident blocks per CU
+int occupancy_mae_product(int64_t zr);  // its resident blocks per CU
 hipError_t launch_mae_select(const MaeArgs &a, hipStream_t s);
 hipError_t launch_mae_recombine(const MaeArgs &a, hipStream_t s);  // and the step size
 hipError_t launch_mae_rank(const MaeArgs &a, float *M, float beta, hipStream_t s);  // M <- beta M + At^T Bt

@@ -35,12 +35,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // either product.
 //
 // Z is split where it is drawn, into tiles of 3 pieces x 4 groups of 8 columns x
-// 112 rows that a block copies to LDS as they are (16 lanes of one column group
+// zr rows that a block copies to LDS as they are (16 lanes of one column group
 // read 256 consecutive bytes); M is read from memory straight into
 // the operand registers -- lane l holds 8 consecutive k of row l % 16, a whole
 // 128-byte line per row -- and split there, so it passes through no LDS and is
-// split once per row tile.  Block: 112 rows x 128 columns, 4 waves of 112 x 32
-// (7 x 2 tiles of v_mfma_f32_16x16x32_bf16, 84 per 32 columns of K).
+// split once per row tile.  Block: zr rows x 128 columns, 4 waves of zr x 32 (for
+// zr = 112 7 x 2 tiles of v_mfma_f32_16x16x32_bf16, 84 per 32 columns of K).  zr is
+// 112, or 32 or 64 where they hold every row, or 64 for two tiles of 113 .. 128
+// rows: with 112 alone 16 samples padded sevenfold and populations of that kind
+// lost up to 9 % to the fp32 product; a generation now takes, before and now, 201
+// and 173 us (16 x 8192), 742 and 627 (30 x 16384), 317 and 287 (120 x 8192).
 //
 // At 101 x 16384 x 16384: 380 us (the fp32 matrix-core product of before took 560
 // in k_gemm_nt16 and its split-K reduction), against 167 us for one pass over M at
@@ -56,8 +60,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // (one fp32 rounding per 32 columns and product of pieces, not per column pair);
 // below D = 3, where one product's own rounding shows, the fp32 path is taken.
 // ---------------------------------------------------------------------------
-constexpr int kSpRows = kMaeSplitRows, kSpCols = 128, kSpRB = kSpRows / 16;
-constexpr int kSpTile = 3 * kSpRows * 32;  // bf16 numbers of one tile of Z
+constexpr int kSpCols = 128;
 constexpr uint32_t kSplitLo = (127 - 80) << 23, kSplitHi = (127 + 120) << 23;  // 2^-80, 2^120
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -115,11 +118,11 @@ __global__ __launch_bounds__(256) void k_mae_sample(MaeArgs a)
         uint32_t p[3][2];
         split2(v.x, v.y, p[0][0], p[1][0], p[2][0]);
         split2(v.z, v.w, p[0][1], p[1][1], p[2][1]);
-        uint16_t *dst = a.Zs + ((row / kSpRows) * kb + c / 8) * kSpTile +
-                        ((c % 8) / 2 * kSpRows + row % kSpRows) * 8 + 4 * (c % 2);
+        const uint32_t rt = (uint32_t)row / (uint32_t)a.zr, rr = (uint32_t)row - rt * (uint32_t)a.zr;
+        uint16_t *dst = a.Zs + (rt * kb + c / 8) * (96 * a.zr) + ((c % 8) / 2 * a.zr + rr) * 8 + 4 * (c % 2);
 #pragma unroll
         for (int u = 0; u < 3; ++u)
-            *reinterpret_cast<uint2 *>(dst + u * kSpRows * 32) = make_uint2(p[u][0], p[u][1]);
+            *reinterpret_cast<uint2 *>(dst + u * a.zr * 32) = make_uint2(p[u][0], p[u][1]);
     }
 }
 
@@ -129,8 +132,10 @@ __global__ __launch_bounds__(256) void k_mae_sample(MaeArgs a)
 // tile in registers and the one after that in the other LDS buffer.
 constexpr int kSpDepth = 3;
 
+template <int RB>  // blocks of 16 rows per tile
 __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *M, int splits, float *work)
 {
+    constexpr int kSpRows = 16 * RB, kSpTile = 96 * kSpRows;  // rows, bf16 numbers of a tile of Z
     __shared__ __align__(16) uint16_t As[2][kSpTile];
     __shared__ int32_t odd;
     constexpr int NA = kSpTile / 8, QA = (NA + 255) / 256;  // 16-byte pieces of a tile, per thread
@@ -182,9 +187,9 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
-    f32x4 acc[kSpRB][2];
+    f32x4 acc[RB][2];
 #pragma unroll
-    for (int m = 0; m < kSpRB; ++m)
+    for (int m = 0; m < RB; ++m)
 #pragma unroll
         for (int n = 0; n < 2; ++n) acc[m][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
     // the range of M's elements: greatest magnitude (NaN aside: it comes out of
@@ -251,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
                 }
                 const uint16_t *src = As[buf] + (kg * kSpRows + r16) * 8;
 #pragma unroll
-                for (int m = 0; m < kSpRB; ++m) {
+                for (int m = 0; m < RB; ++m) {
                     const bf16x8 ah = *reinterpret_cast<const bf16x8 *>(src + m * 16 * 8);
                     const bf16x8 am = *reinterpret_cast<const bf16x8 *>(src + kSpRows * 32 + m * 16 * 8);
                     const bf16x8 al = *reinterpret_cast<const bf16x8 *>(src + 2 * kSpRows * 32 + m * 16 * 8);
@@ -277,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
     if (odd) {
         // fp32 products: lane l holds k 4 u + kg of row r16, u = 0 .. 7
 #pragma unroll
-        for (int m = 0; m < kSpRB; ++m)
+        for (int m = 0; m < RB; ++m)
 #pragma unroll
             for (int n = 0; n < 2; ++n) acc[m][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
         for (int s = s0; s < s1; ++s)
@@ -287,7 +292,7 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
 #pragma unroll
                 for (int n = 0; n < 2; ++n) bv[n] = in[n] && k < a.D ? mrow[n][k] : 0.0f;
 #pragma unroll
-                for (int m = 0; m < kSpRB; ++m) {
+                for (int m = 0; m < RB; ++m) {
                     const int64_t i = i0 + 16 * m + r16;
                     const float av = i < rows && k < a.D ? a.Z[i * a.ldx + k] : 0.0f;
 #pragma unroll
@@ -298,7 +303,7 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
     }
     // result v of tile (m, n): row 16 m + 4 kg + v, column 16 n + r16
 #pragma unroll
-    for (int m = 0; m < kSpRB; ++m)
+    for (int m = 0; m < RB; ++m)
 #pragma unroll
         for (int n = 0; n < 2; ++n)
 #pragma unroll
@@ -599,17 +604,19 @@ hipError_t launch_mae_sample(const MaeArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-int occupancy_mae_product()
+int occupancy_mae_product(int64_t zr)
 {
+    const auto k = zr == 32 ? k_mae_product<2> : zr == 64 ? k_mae_product<4> : k_mae_product<7>;
     int n = 0;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_mae_product, 256, 0) == hipSuccess ? n : 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 256, 0) == hipSuccess ? n : 0;
 }
 
 hipError_t launch_mae_product(const MaeArgs &a, const float *M, int splits, float *work, hipStream_t s)
 {
     if (splits < 1 || (splits > 1 && !work)) return hipErrorInvalidValue;
-    const int64_t tiles = ((a.D + kSpCols - 1) / kSpCols) * ((a.N + 1 + kSpRows - 1) / kSpRows);
-    hipLaunchKernelGGL(k_mae_product, dim3((unsigned)(tiles * splits)), dim3(256), 0, s, a, M, splits, work);
+    const int64_t tiles = ((a.D + kSpCols - 1) / kSpCols) * ((a.N + a.zr) / a.zr);
+    const auto k = a.zr == 32 ? k_mae_product<2> : a.zr == 64 ? k_mae_product<4> : k_mae_product<7>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(tiles * splits)), dim3(256), 0, s, a, M, splits, work);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     return launch_splitk_reduce(GemmArgs{a.N + 1, a.D, a.D, 1.0f, nullptr, 0, nullptr, 0, 0.0f, a.Dm, a.ldx}, splits,

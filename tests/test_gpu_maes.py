@@ -170,10 +170,12 @@ def test_lockstep_generations(evox_gpu, ref, case):
     assert compared >= 1
 
 
-# The sampling product's tiles are 112 rows (samples and the path) by 128
-# columns, K in steps of 32 and slices of at least 64.
+# The sampling product's tiles are 32, 64 or 112 rows (samples and the path; 64
+# for 113 .. 128 of them) by 128 columns, K in steps of 32 and slices of at
+# least 64.
 @pytest.mark.parametrize("N, D", [(111, 31), (112, 32), (110, 33), (5, 63), (223, 127), (224, 128), (40, 129),
-                                  (30, 161), (12, 383)])
+                                  (30, 161), (12, 383),
+                                  (31, 65), (32, 66), (63, 95), (64, 96), (127, 70), (128, 64)])
 def test_dense_matrix_at_tile_edges(evox_gpu, ref, N, D):
     print(f"maes dense M {N} x {D}", flush=True)
     rng = np.random.default_rng(100 * N + D)
