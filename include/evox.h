@@ -18,8 +18,8 @@
  * textbook Ackley, Rastrigin, Griewank, Rosenbrock and Schwefel).
  *
  * Everything runs in hand-written HIP kernels; every call enqueues work on the
- * caller's HIP stream and returns without waiting, except evox_best and
- * evox_profile_read, which synchronize that stream.
+ * caller's HIP stream and returns without waiting, except evox_best,
+ * evox_profile_read and evox_pso_wait (with alone), which synchronize that stream.
  *
  * Ownership: every device buffer is allocated by the caller and only borrowed
  * by the library.  The library allocates no device memory (its one device
@@ -223,6 +223,19 @@ int evox_eval_argmin_noalloc(int fn_id, const float *X, int64_t N, int64_t D, in
  * moved, not yet evaluated positions, and the generation counter has grown by
  * n_gens.  step(a) then step(b) equals step(a + b) bit for bit. */
 int evox_pso_step(evox_state *state, int64_t n_gens);
+
+/* A call of at least four generations of a swarm that fits the registers and
+ * LDS of the device runs in one launch whose blocks wait for each other once per
+ * generation.  Where another stream or process keeps a CU busy, they cannot all
+ * run at once; a wait then ends after `seconds` of the device's clock, and one
+ * block does the call on the untouched swarm: the results are the same, the call
+ * is slower (by default the wait is as long as that block would take, at least
+ * 1 ms).  evox_best and evox_profile_read notice such calls, and the 1000 calls
+ * after that go to the grid-wide kernels.
+ * This sets the wait of a PSO state (seconds < 0: the default; 0: give up at the
+ * first look) and, with alone, waits for the stream and returns how many calls
+ * one block has had to do. */
+int evox_pso_wait(evox_state *state, double seconds, int64_t *alone);
 
 /* Workflow.step x n_gens (Sec. IV-A, Table I; Eq. (1)-(3)) for CSO, the
  * competitive swarm optimizer of Table II (after Cheng and Jin, whose update

@@ -23,6 +23,7 @@ MAX_D = 32768
 EXPORTS = (
     "evox_scratch_bytes", "evox_state_create", "evox_state_destroy", "evox_eval", "evox_eval_ld",
     "evox_eval_argmin_scratch_bytes", "evox_eval_argmin", "evox_eval_argmin_noalloc", "evox_pso_step",
+    "evox_pso_wait",
     "evox_cso_step",
     "evox_de_step", "evox_es_step", "evox_pgpe_step", "evox_maes_step", "evox_nsga2_step",
     "evox_nsga2_sort_scratch_bytes", "evox_nsga2_sort",
@@ -89,6 +90,7 @@ def lib():
             "evox_eval_argmin": ([i32, P, i64, i64, i64, P, P, P, P, sz, P], i32),
             "evox_eval_argmin_noalloc": ([i32, P, i64, i64, i64, P, P, P, P], i32),
             "evox_pso_step": ([P, i64], i32),
+            "evox_pso_wait": ([P, ctypes.c_double, P], i32),
             "evox_cso_step": ([P, i64], i32),
             "evox_de_step": ([P, i64], i32),
             "evox_es_step": ([P, i64], i32),
@@ -367,6 +369,13 @@ class Swarm:
             _check(lib().evox_maes_step(self.handle, n_gens))
         else:
             _check(lib().evox_nsga2_step(self.handle, n_gens))
+
+    def pso_wait(self, seconds):
+        """How long the blocks of a resident PSO call wait for each other (< 0: by
+        the call's size); the number of calls that one block has had to do."""
+        n = ctypes.c_int64(0)
+        _check(lib().evox_pso_wait(self.handle, seconds, ctypes.byref(n)))
+        return n.value
 
     def refresh(self, refit=True):
         _check(lib().evox_cso_refresh(self.handle, 1 if refit else 0))

@@ -240,7 +240,7 @@ int make_plan(const evox_params *P, Plan *pl)
         p.lag = take(sizeof(uint32_t) * (size_t)P->N);
         p.res = pso_res_plan(p.L, P->N);
         if (p.res.nblocks > 1) {
-            p.res_slots = take(sizeof(uint64_t) * 4 * (size_t)p.res.nblocks);
+            p.res_slots = take(sizeof(uint64_t) * (4 * (size_t)p.res.nblocks + 2));  // and two calls' ctl
             p.res_cand = take(sizeof(uint64_t) * 2 * (size_t)p.res.nblocks * 4 * (size_t)p.L.G);
         }
     }
@@ -336,6 +336,10 @@ struct evox_state {
     double *xsum, *s1;
     uint32_t *lag;     // PSO: marks of the rows whose personal best is the x row
     int res_calls;     // PSO: resident calls so far, modulo 2 (-1: not on this device)
+    double res_wait;   // PSO: seconds a resident block waits for the others (< 0: by the call's size)
+    double clock_hz;   // rate of the device's wall clock
+    int32_t res_alone; // PSO: resident calls done by one block, as last read
+    int64_t res_rest;  // PSO: calls still to be made by the grid-wide kernels after such a one
     float *x2, *fit2;  // DE: the other population buffer
     uint32_t *esrank;  // ES: sample ranks
     double *espart;    // ES: gradient partial sums
@@ -387,14 +391,40 @@ hipError_t timed(evox_state *s, F &&launch, int64_t gens = 1)
 hipError_t best_init(evox_state *s, float f, int64_t i) { return launch_best_init(s->best, f, i, s->stream); }
 
 // Whether `blocks` blocks, one per CU, can wait for each other on the current
-// device.
-bool cooperative(int blocks)
+// device, and the rate of its clock.
+bool cooperative(int blocks, double *clock_hz)
 {
-    int dev = 0, cus = 0, coop = 0;
-    return hipGetDevice(&dev) == hipSuccess &&
-           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-           hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
-           cus >= blocks;
+    int dev = 0, cus = 0, coop = 0, khz = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess;
+    *clock_hz = 1e3 * khz;
+    return ok && coop && khz > 0 && cus >= blocks;
+}
+
+// How long the blocks of a resident call wait for each other: about as long as
+// one block would take for the call (1 ns per element and generation for large
+// swarms: 180 ms at 10,000 x 1000 x 20), so that giving up costs at most about
+// twice what waiting for the neighbour would have, and not less than a
+// millisecond.
+double res_wait(const evox_state *s, int64_t n_gens)
+{
+    if (s->res_wait >= 0.0) return s->res_wait;
+    const double work = 1e-9 * (double)n_gens * (double)s->P.N * (double)s->P.D;
+    return work > 1e-3 ? work : 1e-3;
+}
+
+// After a resident call that one block had to do, as evox_best and
+// evox_profile_read see it: the device is shared, the next calls are made by the
+// grid-wide kernels before it is tried again.
+constexpr int64_t kResRest = 1000;
+void res_look(evox_state *s, const DevBest &h)
+{
+    if (s->P.algo == EVOX_PSO && h.alone != s->res_alone) {
+        s->res_alone = h.alone;
+        if (s->res_wait < 0.0) s->res_rest = kResRest;
+    }
 }
 
 bool capturing(hipStream_t s)
@@ -522,7 +552,11 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
     s->xsum = s->s1 = nullptr;
     s->perm_t0 = -1;
     s->ticket = nullptr;
-    s->res_calls = pl.res.nblocks > 1 && !cooperative(pl.res.nblocks) ? -1 : 0;
+    s->clock_hz = 0.0;
+    s->res_calls = pl.res.nblocks > 1 && !cooperative(pl.res.nblocks, &s->clock_hz) ? -1 : 0;
+    s->res_wait = -1.0;
+    s->res_alone = 0;
+    s->res_rest = 0;
     s->lag = P.algo == EVOX_PSO ? at<uint32_t>(b->scratch, pl.lag) : nullptr;
     s->x2 = s->fit2 = nullptr;
     s->esrank = nullptr;
@@ -667,7 +701,7 @@ int evox_state_create(const evox_params *params, const evox_buffers *b, void *hi
         if ((e = best_init(s, std::numeric_limits<float>::infinity(), 0)) != hipSuccess ||
             (e = launch_fill(b->pfit, P.N, std::numeric_limits<float>::infinity(), s->stream)) != hipSuccess ||
             (e = launch_copy_row(b->pbest, b->gbest, P.ldx, s->stream)) != hipSuccess ||
-            (pl.res.nblocks > 1 && (e = launch_fill_u32(at<uint32_t>(b->scratch, pl.res_slots), 8 * pl.res.nblocks,
+            (pl.res.nblocks > 1 && (e = launch_fill_u32(at<uint32_t>(b->scratch, pl.res_slots), 8 * pl.res.nblocks + 4,
                                                         0xffffffffu, s->stream)) != hipSuccess)) {
             delete s;
             return hip_fail(e, "init");
@@ -891,13 +925,17 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
     // n - 1 between the first evaluation and the last move of another's
     const bool small = pl.L.G <= 64 && s->P.N * s->P.D <= 16384;
     if (pl.res.nblocks == 1 ||
-        (pl.res.nblocks > 1 && s->res_calls >= 0 && n_gens >= kResMinGens && !capturing(s->stream))) {
+        (pl.res.nblocks > 1 && s->res_calls >= 0 && n_gens >= kResMinGens && s->res_rest == 0 &&
+         !capturing(s->stream))) {
         // the swarm on the chip for the whole call, one launch (a launch of
         // blocks that wait for each other is not recorded into a graph)
         const int nb = pl.res.nblocks;
         uint64_t *slots = at<uint64_t>(s->B.scratch, pl.res_slots);
+        uint32_t *ctl = reinterpret_cast<uint32_t *>(slots + 4 * nb);
+        const double wait = res_wait(s, n_gens);
         const PsoResArgs ra{n_gens, nb, slots + 2 * nb * s->res_calls, slots + 2 * nb * (1 - s->res_calls),
-                            at<uint64_t>(s->B.scratch, pl.res_cand), s->B.gbest, s->best};
+                            ctl + 2 * s->res_calls, ctl + 2 * (1 - s->res_calls), (uint64_t)(wait * s->clock_hz),
+                            wait < 1e-3 ? 1 : 32, at<uint64_t>(s->B.scratch, pl.res_cand), s->B.gbest, s->best};
         a.t = (uint32_t)s->t;
         e = timed(s, [&] { return launch_pso_res(fn, pl.L.G, pl.res, a, ra, s->stream); },
                   small ? n_gens : n_gens - 1);
@@ -910,6 +948,7 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
         (void)hipGetLastError();  // the device does not take the launch: the grid-wide kernels from now on
         s->res_calls = -1;
     }
+    if (s->res_rest > 0) --s->res_rest;
     // generation t: evaluate x_t, personal and global bests
     const auto first = [&] { return launch_pso(fn, pl.L, PSO_EVAL, a, s->stream); };
     const auto last = [&] { return launch_pso(fn, pl.L, PSO_MOVE, a, s->stream); };
@@ -1178,7 +1217,7 @@ int evox_best(evox_state *s, float *best_fit, int64_t *best_idx, float *best_x_h
     hipError_t e = hipMemcpyAsync(&h, s->best, sizeof h, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "read best");
-    if (h.failed) return fail(EVOX_EHIP, "a wait between the blocks of a resident PSO call ran out");
+    res_look(s, h);
     if (best_fit) *best_fit = h.f;
     if (best_idx) *best_idx = h.i;
     if (best_x_host) {
@@ -1188,6 +1227,22 @@ int evox_best(evox_state *s, float *best_fit, int64_t *best_idx, float *best_x_h
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return hip_fail(e, "read best row");
     }
+    return EVOX_OK;
+}
+
+int evox_pso_wait(evox_state *s, double seconds, int64_t *alone)
+{
+    if (!s) return fail(EVOX_EINVAL, "state is null");
+    if (s->P.algo != EVOX_PSO) return fail(EVOX_EINVAL, "not a PSO state");
+    if (!(seconds <= 1e6)) return fail(EVOX_EINVAL, "seconds = %g above 1e6", seconds);
+    s->res_wait = seconds < 0.0 ? -1.0 : seconds;
+    s->res_rest = 0;
+    if (!alone) return EVOX_OK;
+    DevBest h{};
+    hipError_t e = hipMemcpyAsync(&h, s->best, sizeof h, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    if (e != hipSuccess) return hip_fail(e, "read calls");
+    *alone = s->res_alone = h.alone;
     return EVOX_OK;
 }
 
@@ -1428,7 +1483,7 @@ int evox_profile_read(evox_state *s, double *fused_ms, int64_t *fused_launches, 
     DevBest h{};
     e = hipMemcpy(&h, s->best, sizeof h, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "profile read");
-    if (h.failed) return fail(EVOX_EHIP, "a wait between the blocks of a resident PSO call ran out");
+    res_look(s, h);
     if (fused_ms) *fused_ms = ms;
     if (fused_launches) *fused_launches = s->prof_gens;
     if (improved_rows) *improved_rows = (int64_t)(h.improved - s->improved_base);

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void k_fill(float *dst, int64_t n, float value
 __global__ void k_best_init(DevBest *best, float f, int64_t i)
 {
     best->f = f;
-    best->failed = 0;
+    best->alone = 0;
     best->i = i;
     best->improved = 0;
 }

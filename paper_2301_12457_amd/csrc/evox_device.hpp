@@ -578,7 +578,7 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 // Result of a selection, kept in device scratch.
 struct DevBest {
     float f;
-    int32_t failed;  // a wait between the blocks of a resident call ran out
+    int32_t alone;  // PSO: resident calls whose blocks did not come together, done by one block
     int64_t i;
     uint64_t improved;  // PSO: rows whose personal best improved, summed
 };

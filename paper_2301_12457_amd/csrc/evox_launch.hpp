@@ -274,6 +274,10 @@ struct PsoResArgs {
     int32_t nblocks;
     uint64_t *slots;       // [2][nblocks] this call's slots, cleared by the call before
     uint64_t *slots_next;  // [2][nblocks] the next call's
+    uint32_t *ctl;         // [2] whether the call was completed, blocks out (all ones before it)
+    uint32_t *ctl_next;    // [2] the next call's
+    uint64_t wait;         // a wait ends after this many ticks of the wall clock
+    int32_t polls;         // polls between looks at the clock
     uint64_t *cand;        // [2][nblocks][4 G] the blocks' best rows
     float *gbest_out;      // [ldx]
     DevBest *best;

@@ -18,10 +18,29 @@
 // in which every block has shown to be done with it.  All stores and loads that
 // cross blocks are agent-scope atomics (written through, read past the caches),
 // so no fence writes back an L2.  The number of exchanges is n_gens in every
-// block, whatever the data; the launch is cooperative, so all blocks are
-// resident; a wait is bounded all the same (kResSpins) and reports a failure
-// through DevBest::failed.  The half of the move that does not need the global
+// block, whatever the data.  The half of the move that does not need the global
 // best runs between the store of the slot and the wait.
+//
+// The launch is cooperative: the grid fits the device.  That does not make the
+// blocks start together -- a kernel of another stream or process may hold a CU
+// for as long as it likes -- so a wait ends by the clock (PsoResArgs::wait) and
+// the call is then given up and done by one block instead.  Nothing of the
+// swarm is stored before the end of a call, so it only has to be decided once
+// and for every block alike whether the call was completed, in ctl[0]:
+//   - a block whose wait has run out turns kResRun into kResTry and reads the
+//     slots again; if one is still missing, it turns kResTry into kResAlone and
+//     leaves (else it goes on);
+//   - a block that has passed the last exchange reads ctl[0]: kResRun and it
+//     stores its rows (a block that tries later finds every slot); else it turns
+//     kResTry into kResDone and stores, or finds kResAlone and leaves.
+// One of the two changes of kResTry is made, and every block that finds the word
+// changed follows it.  A block that read kResRun is never contradicted: kResAlone
+// needs a slot missing after kResTry was set, and who sees all the slots of the
+// last exchange after that reads the word later still.  The usual call pays one
+// read (a compare-and-swap by every block on one word cost 4 us a call).  After
+// kResAlone every block leaves, those that start late as well, and the last one
+// out (a count in ctl[1]) runs the whole call on the untouched swarm (pso_walk).
+// The results are the same bits either way.
 //
 // One block (nblocks 1) needs none of this and is an ordinary launch.
 //
@@ -39,7 +58,9 @@
 namespace evox {
 
 constexpr uint64_t kResNoSlot = ~(uint64_t)0;  // tag 255, and generation 254's slots are not the first
-constexpr int kResSpins = 1 << 22;
+// ctl[0] of a call; ctl[1] counts the blocks out, from -1 on (both words are
+// all ones before a call, as its slots are)
+constexpr uint32_t kResRun = 0xffffffffu, kResDone = 0, kResAlone = 1, kResTry = 2;
 
 __device__ __forceinline__ uint32_t tag_of(uint64_t slot) { return ((uint32_t)slot >> 24) & 0xffu; }
 
@@ -58,10 +79,108 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v)
     return v;
 }
 
+// The kernel argument at the given offset, as a value of its own to the compiler.
+template <typename V>
+__device__ __forceinline__ V kernel_argument(uint32_t offset)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    Words src = (Words)(at + offset);
+    uint32_t w[sizeof(V) / 4];
+#pragma unroll
+    for (uint32_t q = 0; q < sizeof(V) / 4; ++q) w[q] = src[q];
+    V v;
+    __builtin_memcpy(&v, w, sizeof v);
+    return v;
+}
+
+// A whole n_gens-generation call by one block, the swarm in memory: per
+// generation one walk over the rows to evaluate (the fitness bits of
+// row_fitness) and one to move them.  nbr, red: LDS as row_fitness takes it;
+// sk, sc: blockDim / 64 entries; sel: one.  The chunks of the move are not
+// unrolled: both at once cost the resident kernel that this is a part of 60
+// spilled registers in its ten-row shape.
+template <int FN, int G>
+__device__ __forceinline__ void pso_walk(const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best, float *nbr, float *red,
+                         uint64_t *sk, uint32_t *sc, int64_t *sel)
+{
+    constexpr int MAXIT = 2;
+    const int tid = (int)opaque<1>(threadIdx.x), nt = blockDim.x, g = tid % G, slot = tid / G, gpb = nt / G;
+    const uint32_t C4 = (uint32_t)((a.D + 3) >> 2);
+    const uint32_t CW = (uint32_t)(a.ldx / 4 < G * MAXIT ? a.ldx / 4 : G * MAXIT);
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int64_t k = 0; k < n_gens; ++k) {
+        uint64_t key = kNoKey;
+        uint32_t nimp = 0;
+        for (int64_t rb = 0; rb < a.N; rb += gpb) {  // uniform trip count: row_fitness has barriers
+            const int64_t row = rb + slot;
+            const bool active = row < a.N;
+            const float pold = active ? a.pf[row] : 0.0f;
+            float4 xr[MAXIT];
+#pragma unroll
+            for (int it = 0; it < MAXIT; ++it) {
+                const uint32_t c = g + G * it;
+                xr[it] = active && c < C4 ? *reinterpret_cast<const float4 *>(a.x + row * a.ldx + 4 * c) : zero;
+            }
+            const float f = row_fitness<FN, G, MAXIT>(xr, g, a.D, nbr, red);
+            if (active) {
+                const bool imp = f < pold;
+                if (imp) {
+#pragma unroll
+                    for (int it = 0; it < MAXIT; ++it) {
+                        const uint32_t c = g + G * it;
+                        if (c < CW) *reinterpret_cast<float4 *>(a.p + row * a.ldx + 4 * c) = xr[it];
+                    }
+                }
+                if (g == 0) {
+                    if (imp) a.pf[row] = f;
+                    if (a.fit) a.fit[row] = f;
+                    const uint64_t kr = sel_key(imp ? f : pold, row);
+                    key = kr < key ? kr : key;
+                    nimp += imp ? 1u : 0u;
+                }
+            }
+        }
+        block_min_key(key, nimp, sk, sc);
+        if (tid == 0) {
+            best->f = key_value(key);
+            best->i = *sel = key_index(key);
+            best->improved += nimp;
+        }
+        __syncthreads();
+        for (int64_t j = tid; j < a.ldx; j += nt) gbest_out[j] = a.p[*sel * a.ldx + j];
+        __syncthreads();
+        for (int64_t rb = 0; rb < a.N; rb += gpb) {
+            const int64_t row = rb + slot;
+#pragma unroll 1
+            for (int it = 0; it < MAXIT; ++it) {
+                const uint32_t c = g + G * it;
+                const int64_t off = row * a.ldx + 4 * c;
+                float4 xn = zero, vn = zero;
+                if (row < a.N && c < C4) {
+                    const float4 xv = *reinterpret_cast<const float4 *>(a.x + off);
+                    const float4 pull =
+                        pso_pull4(a, (uint32_t)row, c, a.t + (uint32_t)k, xv, *reinterpret_cast<const float4 *>(a.v + off),
+                                  *reinterpret_cast<const float4 *>(a.p + off));
+                    pso_push4<true, true>(a, c, pso_draw4(a, (uint32_t)row, c, a.t + (uint32_t)k), xv, pull,
+                                          *reinterpret_cast<const float4 *>(gbest_out + 4 * c), xn, vn);
+                }
+                if (row < a.N && c < CW) {
+                    *reinterpret_cast<float4 *>(a.x + off) = xn;
+                    *reinterpret_cast<float4 *>(a.v + off) = vn;
+                }
+            }
+        }
+        __syncthreads();  // the next generation evaluates every moved row
+    }
+}
+
 // R rows per lane group of G lanes, two chunks per lane; VL of the R velocity
 // rows in LDS, the rest in registers; at most T threads per block (T exactly
-// when VL > 0).
-template <int FN, int G, int R, int VL, int T>
+// when VL > 0).  MANY: more than one block (in one kernel with the other the
+// scalar registers of either spill into the generation loop of both).
+template <int FN, int G, int R, int VL, int T, bool MANY>
 __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
 {
     using F = Fn<FN>;
@@ -70,17 +189,19 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
     __shared__ float4 vls[VL > 0 ? VL * MAXIT * T : 1];
     // one block: each unit's (wave's, or spanning row's) best row by parity;
     // else the global best row
-    constexpr bool ONE = R == 1 && VL == 0;  // the shape that runs in one block too
-    constexpr int UNIT = G > 64 ? G : 64, NU = ONE ? 2 * (T / UNIT) : 1;
+    constexpr bool ONE = R == 1;
+    static_assert(MANY || ONE, "one block: a row per group");
+    constexpr int UNIT = G > 64 ? G : 64, NU = MANY ? 1 : 2 * (T / UNIT);
     __shared__ __align__(16) float gb[NU][G * MAXIT * 4];
     __shared__ uint64_t sk[2][NW], sm[NW];
     __shared__ Acc red[SPAN ? R : 1][NW];
     __shared__ float first[SPAN && F::kNeighbour ? R : 1][MAXIT][NW];
-    __shared__ int32_t bad;
+    __shared__ int32_t bad, lost, last;  // a wait ran out; the call is given up; the last block out
+    __shared__ int64_t pick;
 
     const int tid = threadIdx.x, nt = blockDim.x, nw = nt / 64, lane = tid & 63, wave = tid >> 6;
     const int g = tid % G, slot = tid / G, gpb = nt / G;  // groups per block
-    const int nb = e.nblocks, b = blockIdx.x;
+    const int nb = MANY ? e.nblocks : 1, b = MANY ? blockIdx.x : 0;
     const uint32_t C4 = (uint32_t)((a.D + 3) >> 2);
     const uint32_t CW = (uint32_t)(a.ldx / 4 < G * MAXIT ? a.ldx / 4 : G * MAXIT);
     const uint32_t N = (uint32_t)a.N;
@@ -90,7 +211,7 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
     // compute on zeros; nothing of theirs is selected or stored
     const uint32_t row0 = (uint32_t)(b * gpb + slot), step = (uint32_t)(nb * gpb);
     const bool clamp = a.vclamp || a.xclamp;  // uniform
-    auto live = [&](int r) { return (uint32_t)(b * gpb) + r * step < N; };
+    auto live = [&](int r) { return opaque<64>((uint32_t)(b * gpb)) + r * step < N; };  // compared anew: no masks kept
 
     float4 x[R][MAXIT], p[R][MAXIT], vr[VR > 0 ? VR : 1][MAXIT];
     float pf[R];
@@ -123,7 +244,8 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             setv(r, it, row4(a.v));
         }
     }
-    if (tid == 0) bad = 0;
+    if (tid == 0) bad = lost = 0;
+    uint32_t word = kResRun;  // thread 0: ctl[0] after the last exchange
     uint64_t win = kNoKey, sent[2] = {kNoKey, kNoKey};  // last winner; block bests whose rows the buffers hold
     uint32_t nimp = 0;
     const float4 *gsrc = reinterpret_cast<const float4 *>(gb[0]);
@@ -135,8 +257,9 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
         // fitness of every row in the order of row_fitness, personal bests,
         // and the block's best (value, row)
         uint64_t key = kNoKey;
+        const uint32_t rowe = opaque<G>(row0);
         auto decide = [&](int r, Acc s) {
-            const uint32_t row = row0 + r * step;
+            const uint32_t row = rowe + r * step;
             const float f = F::finish(s, a.D);
             const bool in = row < N, imp = in && f < pf[r];
             pf[r] = imp ? f : pf[r];
@@ -206,8 +329,8 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
         const uint64_t own = key;
         if constexpr (G < 64) key = lanes_min<32, G>(key);
         if (lane == 0) sk[q][wave] = key;
-        if constexpr (ONE)
-            if (nb == 1 && own == key && key != kNoKey) {
+        if constexpr (!MANY)
+            if (own == key && key != kNoKey) {
                 float4 *dst = reinterpret_cast<float4 *>(gb[q * (T / UNIT) + tid / UNIT]);
 #pragma unroll
                 for (int it = 0; it < MAXIT; ++it) dst[g + G * it] = p[0][it];
@@ -230,10 +353,10 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        if (nb == 1) pull();
+        if constexpr (!MANY) pull();
         __syncthreads();
         key = lanes_min<8>(sk[q][(lane & 15) < nw ? lane & 15 : 0]);
-        if (nb > 1) {
+        if constexpr (MANY) {
             const bool fresh = key != sent[q];  // uniform over the block
             sent[q] = key;
             if (fresh) {
@@ -257,8 +380,8 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             if (tid == 0)
                 store_through(e.slots + q * nb + b, (key & ~(uint64_t)0xffffffffu) | tag | (key & 0xffffffu));
         }
-        if (nb > 1) pull();
-        if (nb > 1) {
+        if constexpr (MANY) {
+            pull();
             const uint32_t want = (uint32_t)(k + 1) & 0xffu;
             uint64_t m = kNoKey;
             if (tid < nb) {
@@ -267,21 +390,40 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
                 uint64_t w[P];
                 const uint64_t *base = e.slots + q * nb;
                 const bool one = nt >= nb;
-                bool all;
-                int spins = 0;
-                do {
-                    all = true;
-                    if (one) {
-                        w[0] = load_past(base + tid);
-                        all = tag_of(w[0]) == want;
-                    } else {
+                auto poll = [&] {
+                    if (!one) {
 #pragma unroll
-                        for (int u = 0; u < P; ++u) w[u] = load_past(base + (tid + u * nt < nb ? tid + u * nt : tid));
-#pragma unroll
-                        for (int u = 0; u < P; ++u) all &= tag_of(w[u]) == want;
+                        for (int u = 1; u < P; ++u) w[u] = load_past(base + (tid + u * nt < nb ? tid + u * nt : tid));
                     }
-                } while (!all && ++spins < kResSpins);
-                if (!all) bad = 1;
+                    w[0] = load_past(base + tid);
+                    bool all = tag_of(w[0]) == want;
+                    if (!one) {
+#pragma unroll
+                        for (int u = 1; u < P; ++u) all &= tag_of(w[u]) == want;
+                    }
+                    return all;
+                };
+                uint64_t since = 0;
+                for (;;) {
+                    bool all;
+                    int polls = 0;
+                    do all = poll();
+                    while (!all && ++polls < e.polls);
+                    if (all) break;
+                    const uint64_t now = wall_clock64();
+                    if (since == 0) since = now;
+                    uint32_t st = load_past(e.ctl);
+                    if ((st == kResRun || st == kResTry) && now - since >= e.wait) {
+                        atomicCAS(e.ctl, kResRun, kResTry);
+                        wait_stores();  // the word is set before the slots are read again
+                        if (poll()) break;
+                        st = atomicCAS(e.ctl, kResTry, kResAlone) == kResDone ? kResDone : kResAlone;
+                    }
+                    if (st == kResAlone) {
+                        bad = 1;
+                        break;
+                    }
+                }
                 m = w[0];
                 if (!one) {
 #pragma unroll
@@ -294,10 +436,10 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             key = lanes_min<8>(sm[(lane & 15) < nw ? lane & 15 : 0]);
             if (bad) break;  // uniform: written before the barrier
             key &= ~(uint64_t)0xff000000u;  // the tag out, the index back
+            if (k == e.n_gens - 1 && tid == 0) word = load_past(e.ctl);
         }
-        if (nb == 1) {
-            if constexpr (ONE)
-                gsrc = reinterpret_cast<const float4 *>(gb[q * (T / UNIT) + (uint32_t)key * G / UNIT]);
+        if constexpr (!MANY) {
+            gsrc = reinterpret_cast<const float4 *>(gb[q * (T / UNIT) + (uint32_t)key * G / UNIT]);
         } else if (key != win) {
             const uint64_t *src =
                 e.cand + ((int64_t)q * nb + (uint32_t)key / (uint32_t)gpb % (uint32_t)nb) * (G * MAXIT * 2);
@@ -334,6 +476,36 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
         // gb are next written behind a barrier that every wave reaches after
         // its last read here
     }
+    if constexpr (MANY) {
+        // the other launch parity's words, idle now, are cleared for the next call
+        if (tid < 2) {
+            store_through(e.slots_next + tid * nb + b, kResNoSlot);
+            if (b == 0) store_through(e.ctl_next + tid, kResRun);
+        }
+        if (word != kResRun) lost = atomicCAS(e.ctl, kResTry, kResDone) == kResAlone;
+        __syncthreads();
+        // the same in every block; scalar branches, so that the rows are dead in it
+        if (__builtin_amdgcn_readfirstlane(bad | lost)) {
+            if (tid == 0) last = atomicAdd(e.ctl + 1, 1u) + 1u == (uint32_t)(nb - 1);
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(last)) {
+                // fit may hold values of this call's last generation: those that
+                // the walk stores again
+                if (tid == 0) ++e.best->alone;
+                float *nbr = nullptr;
+                if constexpr (SPAN && F::kNeighbour) {
+                    __shared__ float own[VL > 0 ? 1 : T * MAXIT];
+                    nbr = VL > 0 ? reinterpret_cast<float *>(vls) : own;
+                }
+                // the arguments read again: none is carried here through the loop
+                const PsoArgs wa = kernel_argument<PsoArgs>(0);
+                const PsoResArgs we = kernel_argument<PsoResArgs>(sizeof(PsoArgs));
+                pso_walk<FN, G>(wa, we.n_gens, we.gbest_out, we.best, nbr, reinterpret_cast<float *>(red), sk[0],
+                                reinterpret_cast<uint32_t *>(sm), &pick);
+            }
+            return;
+        }
+    }
 
     {
         // opaque: the addresses are not carried through the loop from the loads
@@ -358,8 +530,6 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
     }
     nimp = lanes_sum<32>(nimp);
     if (lane == 0 && nimp) atomicAdd((unsigned long long *)&e.best->improved, (unsigned long long)nimp);
-    // the other launch parity's slots, idle now, are cleared for the next call
-    if (nb > 1 && tid < 2) store_through(e.slots_next + tid * nb + b, kResNoSlot);
     if (b == 0) {
         for (int j = tid; j < a.ldx; j += nt) e.gbest_out[j] = j < G * MAXIT * 4 ? reinterpret_cast<const float *>(gsrc)[j] : 0.0f;
         if (tid == 0) {
@@ -367,7 +537,6 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             e.best->i = key_index(win);
         }
     }
-    if (bad && tid == 0) e.best->failed = 1;
 }
 
 // The three shapes (PsoResPlan::shape): one row per group with up to 1024
@@ -378,13 +547,14 @@ template <int FN, int G>
 hipError_t launch_pso_res_g(const PsoResPlan &pl, PsoArgs &a, PsoResArgs &e, hipStream_t s)
 {
     constexpr int VL = G == 512 ? 8 : 9;
-    const void *f = pl.shape == 1   ? reinterpret_cast<const void *>(&k_pso_res<FN, G, 1, 0, 1024>)
-                    : pl.shape == 2 ? reinterpret_cast<const void *>(&k_pso_res<FN, G, 4, 0, 512>)
-                                    : reinterpret_cast<const void *>(&k_pso_res<FN, G, 10, VL, 512>);
     void *args[] = {&a, &e};
-    return e.nblocks == 1
-               ? hipLaunchKernel(f, dim3(1), dim3((unsigned)pl.threads), args, 0, s)
-               : hipLaunchCooperativeKernel(f, dim3((unsigned)e.nblocks), dim3((unsigned)pl.threads), args, 0, s);
+    if (e.nblocks == 1)
+        return hipLaunchKernel(reinterpret_cast<const void *>(&k_pso_res<FN, G, 1, 0, 1024, false>), dim3(1),
+                               dim3((unsigned)pl.threads), args, 0, s);
+    const void *f = pl.shape == 1   ? reinterpret_cast<const void *>(&k_pso_res<FN, G, 1, 0, 1024, true>)
+                    : pl.shape == 2 ? reinterpret_cast<const void *>(&k_pso_res<FN, G, 4, 0, 512, true>)
+                                    : reinterpret_cast<const void *>(&k_pso_res<FN, G, 10, VL, 512, true>);
+    return hipLaunchCooperativeKernel(f, dim3((unsigned)e.nblocks), dim3((unsigned)pl.threads), args, 0, s);
 }
 
 template <int FN>

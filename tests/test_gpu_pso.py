@@ -6,6 +6,8 @@ generation.  Positions and velocities are compared bit for bit, personal-best
 fitness within the fitness tolerance, and the global-best index exactly
 (a tolerance tie would be reported as such).
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -281,3 +283,67 @@ def test_resident_selection_with_nan_and_infinite_rows(evox_gpu, ref):
         assert g.best()[1] == r.gi == good
         assert np.array_equal(host(g.pbest, D), r.p)
         assert np.array_equal(host(g.x, D), r.x, equal_nan=True)
+
+
+STATE = ("x", "v", "pbest", "pfit", "fit", "gbest")
+
+
+# every shape of the resident kernel, with rows of part of a wave, of a wave and
+# of several, and a function that looks at a neighbour across waves; the waits:
+# none, about an exchange (a call is given up anywhere in it, or not at all) and
+# the default
+GIVE_UP_CASES = [(2, 300, 10), (4, 1_999, 101), (1, 700, 500), (4, 520, 1_000), (3, 65, 2_100), (4, 40, 4_096),
+                 (5, 20_000, 13), (0, 4_500, 500), (4, 30_000, 70), (1, 2_100, 2_050)]
+
+
+@pytest.mark.parametrize("fn,N,D", GIVE_UP_CASES)
+def test_resident_calls_given_up_are_done_by_one_block(evox_gpu, fn, N, D):
+    lb, ub = {0: (-32.0, 32.0), 1: (-32.768, 32.768), 2: (-5.12, 5.12), 3: (-600.0, 600.0), 4: (-2.0, 2.0),
+              5: (-500.0, 500.0)}[fn]
+    print(f"pso given up fn={fn} N={N} D={D}", flush=True)
+    kw = dict(seed=37, v_lo=-1.0, v_hi=1.0, **(dict(vmax=0.2 * (ub - lb), clamp_x=1) if N % 2 else {}))
+    g, one = (evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, fn, N, D, lb, ub, **kw)) for _ in range(2))
+    given_up = 0
+    for wait, n in ((0.0, 4), (0.0, 5), (1e-6, 6), (2e-6, 9), (3e-6, 5), (0.0, 4), (-1.0, 4)):
+        before = g.pso_wait(wait)
+        g.step(n)
+        for _ in range(n):
+            one.step(1)  # grid-wide
+        for name in STATE:
+            assert torch.equal(getattr(g, name), getattr(one, name)), (name, wait, n)
+        assert g.best() == one.best()
+        after = g.pso_wait(-1.0)
+        assert after - before in ((1,) if wait == 0.0 else (0, 1) if wait > 0.0 else (0,)), (wait, before, after)
+        given_up += after - before
+    assert given_up >= 3
+
+
+def test_wait_argument(evox_gpu):
+    g = evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 0, 20, 5, -1.0, 1.0))
+    assert g.pso_wait(0.0) == 0 and g.pso_wait(-1.0) == 0
+    for bad in (math.nan, 1e7):
+        with pytest.raises(evox_gpu.EvoxError):
+            g.pso_wait(bad)
+    with pytest.raises(evox_gpu.EvoxError):
+        evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.CSO, 0, 20, 5, -1.0, 1.0)).pso_wait(0.0)
+
+
+def test_resident_call_beside_a_long_kernel(evox_gpu):
+    """A one-block call of many generations holds a CU while calls that need
+    every CU are made on another stream: they give the same swarm as without it."""
+    busy, st = torch.cuda.Stream(), torch.cuda.Stream()
+    mk = lambda N, D, s: evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 1, N, D, -32.0, 32.0, seed=11), stream=s)  # noqa: E731
+    long, g = mk(100, 10, busy), mk(10_000, 1_000, st)
+    one = mk(10_000, 1_000, st)
+    torch.cuda.synchronize()
+    long.step(400_000)  # under a second in one block
+    for _ in range(3):
+        g.step(4)
+    for _ in range(12):
+        one.step(1)
+    torch.cuda.synchronize()
+    for name in STATE:
+        assert torch.equal(getattr(g, name), getattr(one, name)), name
+    assert g.best() == one.best()
+    print("calls done by one block:", g.pso_wait(-1.0), flush=True)
+    assert long.t == 400_000 and math.isfinite(long.best()[0])
