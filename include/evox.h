@@ -232,8 +232,8 @@ int evox_pso_step(evox_state *state, int64_t n_gens);
  * is slower (by default the wait is as long as that block would take, at least
  * 1 ms).  evox_best and evox_profile_read notice such calls, and the 1000 calls
  * after that go to the grid-wide kernels.
- * This sets the wait of a PSO state (seconds < 0: the default; 0: give up at the
- * first look) and, with alone, waits for the stream and returns how many calls
+ * This sets the wait of a PSO state (seconds < 0: the default; 0: such calls are
+ * always given up) and, with alone, waits for the stream and returns how many calls
  * one block has had to do. */
 int evox_pso_wait(evox_state *state, double seconds, int64_t *alone);
 

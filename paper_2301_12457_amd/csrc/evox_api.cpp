@@ -139,6 +139,8 @@ struct Plan {
     int perm_batch = 0;
     size_t lag = 0;           // PSO: marks of the rows whose personal best is the x row
     PsoResPlan res{0, 0, 0};  // PSO: the resident call's shape, its slots and best rows
+    PsoResPlan res_one{0, 0, 0};  // the same in one block, several rows per lane group
+    int64_t res_one_gens = 0;     // its calls are of at most so many generations where res can be launched
     size_t res_slots = 0, res_cand = 0;
     size_t x2 = 0, fit2 = 0;  // DE: the other population buffer and its fitness
     size_t xalt = 0;          // CSO neighbourhood version: the other population buffer
@@ -239,6 +241,7 @@ int make_plan(const evox_params *P, Plan *pl)
     if (P->algo == EVOX_PSO) {
         p.lag = take(sizeof(uint32_t) * (size_t)P->N);
         p.res = pso_res_plan(p.L, P->N);
+        if (p.res.nblocks > 1) p.res_one = pso_res_plan_one(p.L, P->N, &p.res_one_gens);
         if (p.res.nblocks > 1) {
             p.res_slots = take(sizeof(uint64_t) * (4 * (size_t)p.res.nblocks + 2));  // and two calls' ctl
             p.res_cand = take(sizeof(uint64_t) * 2 * (size_t)p.res.nblocks * 4 * (size_t)p.L.G);
@@ -924,12 +927,14 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
     // what evox_profile counts: all n generations of a small swarm's call, the
     // n - 1 between the first evaluation and the last move of another's
     const bool small = pl.L.G <= 64 && s->P.N * s->P.D <= 16384;
-    if (pl.res.nblocks == 1 ||
-        (pl.res.nblocks > 1 && s->res_calls >= 0 && n_gens >= kResMinGens && s->res_rest == 0 &&
-         !capturing(s->stream))) {
+    const bool graph = pl.res.nblocks != 1 && capturing(s->stream);
+    const bool many = pl.res.nblocks > 1 && s->res_calls >= 0 && s->res_rest == 0 && !graph;
+    const bool one = pl.res_one.nblocks == 1 && !(many && n_gens > pl.res_one_gens);
+    if (pl.res.nblocks == 1 || one || (many && n_gens >= kResMinGens)) {
         // the swarm on the chip for the whole call, one launch (a launch of
         // blocks that wait for each other is not recorded into a graph)
-        const int nb = pl.res.nblocks;
+        const PsoResPlan &res = one ? pl.res_one : pl.res;
+        const int nb = res.nblocks;
         uint64_t *slots = at<uint64_t>(s->B.scratch, pl.res_slots);
         uint32_t *ctl = reinterpret_cast<uint32_t *>(slots + 4 * nb);
         const double wait = res_wait(s, n_gens);
@@ -937,7 +942,7 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
                             ctl + 2 * s->res_calls, ctl + 2 * (1 - s->res_calls), (uint64_t)(wait * s->clock_hz),
                             wait < 1e-3 ? 1 : 32, at<uint64_t>(s->B.scratch, pl.res_cand), s->B.gbest, s->best};
         a.t = (uint32_t)s->t;
-        e = timed(s, [&] { return launch_pso_res(fn, pl.L.G, pl.res, a, ra, s->stream); },
+        e = timed(s, [&] { return launch_pso_res(fn, pl.L.G, res, a, ra, s->stream); },
                   small ? n_gens : n_gens - 1);
         if (e == hipSuccess) {
             if (nb > 1) s->res_calls ^= 1;

@@ -811,6 +811,23 @@ PsoResPlan pso_res_plan(Layout L, int64_t N)
     return none;
 }
 
+// Chunks that the lanes of the block hold (a generation costs about 0.3 us and
+// 0.9 per 1024 of them) decide where it is the better one.  Against several
+// blocks, which cost 22.5 us a call and 1.85 per generation from four
+// generations on and 8 to 10 per generation before: 257 x 10 (1152 chunks)
+// 8.0, 12.6 and 17.2 us for 2, 4 and 6 generations against 17.1, 29.9 and 33.5;
+// 500 x 16 (2048) 10.5, 16.6, 22.6 against 17.4, 30.4, 33.8; 64 x 250 (4096) 14.6,
+// 24.3, 33.9 against 19.0, 30.4, 34.4; 48 x 490 (6144) 19.1, 32.6, 46.2 against
+// 18.4, 31.3, 35.1: not taken.
+PsoResPlan pso_res_plan_one(Layout L, int64_t N, int64_t *most_gens)
+{
+    const int64_t rows = (N * L.G + 1023) / 1024;  // per group
+    const int64_t threads = ((N + rows - 1) / rows * L.G + 63) / 64 * 64, chunks = rows * threads * L.nit;
+    if (L.maxit != LAYOUT_PSO || L.G > 64 || rows > 3 || chunks > 5120) return PsoResPlan{0, 0, 0};
+    *most_gens = 20480 / (chunks > 1024 ? chunks - 768 : 256);
+    return PsoResPlan{4, (int)threads, 1};
+}
+
 hipError_t launch_pso_res(int fn, int G, const PsoResPlan &pl, const PsoArgs &a, const PsoResArgs &e, hipStream_t s)
 {
 #define EVOX_CALL_PSO_RES(F) launch_pso_res_t<F>(G, pl, a, e, s)

@@ -269,6 +269,10 @@ struct PsoResPlan {
     int shape, threads, nblocks;
 };
 PsoResPlan pso_res_plan(Layout L, int64_t N);
+// One block with up to three rows per lane group, for rows of at most a wave
+// (shape 0: not), and the most generations of a call that it does in the place
+// of several blocks (it does every call for which those cannot be launched).
+PsoResPlan pso_res_plan_one(Layout L, int64_t N, int64_t *most_gens);
 struct PsoResArgs {
     int64_t n_gens;
     int32_t nblocks;

@@ -27,16 +27,17 @@
 // the call is then given up and done by one block instead.  Nothing of the
 // swarm is stored before the end of a call, so it only has to be decided once
 // and for every block alike whether the call was completed, in ctl[0]:
-//   - a block whose wait has run out turns kResRun into kResTry and reads the
-//     slots again; if one is still missing, it turns kResTry into kResAlone and
-//     leaves (else it goes on);
+//   - a block whose wait has run out turns kResRun into kResTry and, at the last
+//     exchange, reads the slots again; if one is still missing, or at an earlier
+//     exchange, it turns kResTry into kResAlone and leaves (else it goes on);
 //   - a block that has passed the last exchange reads ctl[0]: kResRun and it
 //     stores its rows (a block that tries later finds every slot); else it turns
 //     kResTry into kResDone and stores, or finds kResAlone and leaves.
 // One of the two changes of kResTry is made, and every block that finds the word
 // changed follows it.  A block that read kResRun is never contradicted: kResAlone
-// needs a slot missing after kResTry was set, and who sees all the slots of the
-// last exchange after that reads the word later still.  The usual call pays one
+// needs a slot of the last exchange missing after kResTry was set (the leaving
+// block's own if it leaves earlier), and who sees all of them after that reads
+// the word later still.  The usual call pays one
 // read (a compare-and-swap by every block on one word cost 4 us a call).  After
 // kResAlone every block leaves, those that start late as well, and the last one
 // out (a count in ctl[1]) runs the whole call on the untouched swarm (pso_walk).
@@ -44,13 +45,13 @@
 //
 // One block (nblocks 1) needs none of this and is an ordinary launch.
 //
-// What bounds it: the exchange (two trips to memory, about 2.5 us) for small
-// swarms, the vector ALU's issue rate for large ones (10,000 x 1000: 38 chunk
-// waves per SIMD and generation) and for one block's (7 waves on 4 SIMDs at
-// 100 x 10).  Per generation, against launches of k_pso or the one-block
-// kernel it replaced: Sphere 100 x 10 2.35 -> 1.12 us, Rastrigin 1638 x 10
-// 14.0 -> 3.0, Schwefel 1999 x 101 9.5 -> 2.7, Rastrigin 40,000 x 100 23.6 ->
-// 10.3, Ackley 10,000 x 1000 43.5 -> 20 (call of 20: 870 -> 453 us).
+// What bounds it: the exchange (two trips to memory, about 1.8 us with the
+// arithmetic of small swarms), the vector ALU's issue rate for large ones
+// (10,000 x 1000: 38 chunk waves per SIMD and generation) and for one block's (7
+// waves on 4 SIMDs at 100 x 10).  A call of 25, 25, 20, 20 and 20 generations,
+// against launches of k_pso or the one-block kernel it replaced: Sphere 100 x 10
+// 61.2 -> 27.0 us, Rastrigin 1638 x 10 350 -> 69.5, Schwefel 1999 x 101 194 -> 73,
+// Sphere 40,000 x 100 467 -> 190, Ackley 10,000 x 1000 860 -> 440.
 #pragma once
 
 #include "evox_kernels.hpp"
@@ -98,12 +99,12 @@ __device__ __forceinline__ V kernel_argument(uint32_t offset)
 // A whole n_gens-generation call by one block, the swarm in memory: per
 // generation one walk over the rows to evaluate (the fitness bits of
 // row_fitness) and one to move them.  nbr, red: LDS as row_fitness takes it;
-// sk, sc: blockDim / 64 entries; sel: one.  The chunks of the move are not
+// sk, sc: blockDim / 64 entries; sel: one; gb: 8 G floats.  The chunks of the move are not
 // unrolled: both at once cost the resident kernel that this is a part of 60
 // spilled registers in its ten-row shape.
 template <int FN, int G>
 __device__ __forceinline__ void pso_walk(const PsoArgs &a, int64_t n_gens, float *gbest_out, DevBest *best, float *nbr, float *red,
-                         uint64_t *sk, uint32_t *sc, int64_t *sel)
+                         uint64_t *sk, uint32_t *sc, int64_t *sel, float *gb)
 {
     constexpr int MAXIT = 2;
     const int tid = (int)opaque<1>(threadIdx.x), nt = blockDim.x, g = tid % G, slot = tid / G, gpb = nt / G;
@@ -149,7 +150,11 @@ __device__ __forceinline__ void pso_walk(const PsoArgs &a, int64_t n_gens, float
             best->improved += nimp;
         }
         __syncthreads();
-        for (int64_t j = tid; j < a.ldx; j += nt) gbest_out[j] = a.p[*sel * a.ldx + j];
+        for (int64_t j = tid; j < a.ldx; j += nt) {
+            const float t = a.p[*sel * a.ldx + j];
+            gbest_out[j] = t;
+            if (j < 4 * G * MAXIT) gb[j] = t;
+        }
         __syncthreads();
         for (int64_t rb = 0; rb < a.N; rb += gpb) {
             const int64_t row = rb + slot;
@@ -164,7 +169,7 @@ __device__ __forceinline__ void pso_walk(const PsoArgs &a, int64_t n_gens, float
                         pso_pull4(a, (uint32_t)row, c, a.t + (uint32_t)k, xv, *reinterpret_cast<const float4 *>(a.v + off),
                                   *reinterpret_cast<const float4 *>(a.p + off));
                     pso_push4<true, true>(a, c, pso_draw4(a, (uint32_t)row, c, a.t + (uint32_t)k), xv, pull,
-                                          *reinterpret_cast<const float4 *>(gbest_out + 4 * c), xn, vn);
+                                          *reinterpret_cast<const float4 *>(gb + 4 * c), xn, vn);
                 }
                 if (row < a.N && c < CW) {
                     *reinterpret_cast<float4 *>(a.x + off) = xn;
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
     // one block: each unit's (wave's, or spanning row's) best row by parity;
     // else the global best row
     constexpr bool ONE = R == 1;
-    static_assert(MANY || ONE, "one block: a row per group");
+    static_assert(MANY || R <= 3, "one block: up to three rows per group");
     constexpr int UNIT = G > 64 ? G : 64, NU = MANY ? 1 : 2 * (T / UNIT);
     __shared__ __align__(16) float gb[NU][G * MAXIT * 4];
     __shared__ uint64_t sk[2][NW], sm[NW];
@@ -222,36 +227,73 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
         else
             vr[r < VL ? 0 : r - VL][it] = v;
     };
+    // elements past D are zero from here on, whatever the padding holds
+    auto keep = [&](float4 t, bool ld, uint32_t c) {
+        const int left = ld ? (int)a.D - (int)(4 * c) : 0;
+        return make_float4(left > 0 ? t.x : 0.0f, left > 1 ? t.y : 0.0f, left > 2 ? t.z : 0.0f, left > 3 ? t.w : 0.0f);
+    };
+    if constexpr (R <= 3) {
+        // few rows: all their loads in flight together, unconditional (the last
+        // row and chunk past the end)
+        float4 vt[R][MAXIT];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t row = row0 + r * step;
-        const bool in = row < N;
-        __builtin_amdgcn_sched_barrier(0);
-        pf[r] = in ? a.pf[row] : 0.0f;
+        for (int r = 0; r < R; ++r) {
+            const uint32_t row = row0 + r * step < N ? row0 + r * step : N - 1;
+            pf[r] = a.pf[row];
 #pragma unroll
-        for (int it = 0; it < MAXIT; ++it) {
-            const uint32_t c = g + G * it;
-            const int64_t off = (int64_t)row * a.ldx + 4 * c;
-            const bool ld = in && c < C4;
-            // elements past D are zero from here on, whatever the padding holds
-            auto row4 = [&](const float *src) {
-                const float4 t = ld ? *reinterpret_cast<const float4 *>(src + off) : zero;
-                const int left = (int)a.D - (int)(4 * c);
-                return make_float4(t.x, left > 1 ? t.y : 0.0f, left > 2 ? t.z : 0.0f, left > 3 ? t.w : 0.0f);
-            };
-            x[r][it] = row4(a.x);
-            p[r][it] = row4(a.p);
-            setv(r, it, row4(a.v));
+            for (int it = 0; it < MAXIT; ++it) {
+                const uint32_t c = g + G * it;
+                const int64_t off = (int64_t)row * a.ldx + 4 * (c < C4 ? c : C4 - 1);
+                x[r][it] = *reinterpret_cast<const float4 *>(a.x + off);
+                p[r][it] = *reinterpret_cast<const float4 *>(a.p + off);
+                vt[r][it] = *reinterpret_cast<const float4 *>(a.v + off);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = row0 + r * step < N;
+            pf[r] = in ? pf[r] : 0.0f;
+#pragma unroll
+            for (int it = 0; it < MAXIT; ++it) {
+                x[r][it] = keep(x[r][it], in, g + G * it);
+                p[r][it] = keep(p[r][it], in, g + G * it);
+                setv(r, it, keep(vt[r][it], in, g + G * it));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t row = row0 + r * step;
+            const bool in = row < N;
+            __builtin_amdgcn_sched_barrier(0);
+            pf[r] = in ? a.pf[row] : 0.0f;
+#pragma unroll
+            for (int it = 0; it < MAXIT; ++it) {
+                const uint32_t c = g + G * it;
+                const int64_t off = (int64_t)row * a.ldx + 4 * c;
+                const bool ld = in && c < C4;
+                auto row4 = [&](const float *src) {
+                    return keep(ld ? *reinterpret_cast<const float4 *>(src + off) : zero, true, c);
+                };
+                x[r][it] = row4(a.x);
+                p[r][it] = row4(a.p);
+                setv(r, it, row4(a.v));
+            }
         }
     }
-    if (tid == 0) bad = lost = 0;
-    uint32_t word = kResRun;  // thread 0: ctl[0] after the last exchange
+    const int looks = (int)opaque<64>((uint32_t)e.polls);  // in a register: not loaded at every poll
+    const int64_t n_gens = MANY && e.wait == 0 ? 0 : e.n_gens;  // 0: given up at once
+    if (tid == 0) {
+        bad = MANY && e.wait == 0;
+        lost = 0;
+        if (MANY && e.wait == 0) store_through(e.ctl, kResAlone);
+    }
     uint64_t win = kNoKey, sent[2] = {kNoKey, kNoKey};  // last winner; block bests whose rows the buffers hold
     uint32_t nimp = 0;
     const float4 *gsrc = reinterpret_cast<const float4 *>(gb[0]);
     __syncthreads();
 
-    for (int64_t k = 0; k < e.n_gens; ++k) {
+    for (int64_t k = 0; k < n_gens; ++k) {
         const uint32_t t = a.t + (uint32_t)k;
         const int q = (int)(k & 1);
         // fitness of every row in the order of row_fitness, personal bests,
@@ -267,7 +309,7 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
 #pragma unroll
             for (int it = 0; it < MAXIT; ++it)
                 if (imp) p[r][it] = x[r][it];
-            if (k == e.n_gens - 1 && in && g == 0 && a.fit) a.fit[opaque<1>(row)] = f;
+            if (k == n_gens - 1 && in && g == 0 && a.fit) a.fit[opaque<1>(row)] = f;
             const uint64_t kr = in ? sel_key(pf[r], row) : kNoKey;
             key = kr < key ? kr : key;
         };
@@ -333,7 +375,11 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             if (own == key && key != kNoKey) {
                 float4 *dst = reinterpret_cast<float4 *>(gb[q * (T / UNIT) + tid / UNIT]);
 #pragma unroll
-                for (int it = 0; it < MAXIT; ++it) dst[g + G * it] = p[0][it];
+                for (int r = 0; r < R; ++r)
+                    if (row0 + r * step == (uint32_t)key) {
+#pragma unroll
+                        for (int it = 0; it < MAXIT; ++it) dst[g + G * it] = p[r][it];
+                    }
             }
         // the half of the move that needs no global best, before the wait for
         // the other waves (one row per group: both halves' random numbers) or
@@ -384,8 +430,9 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             pull();
             const uint32_t want = (uint32_t)(k + 1) & 0xffu;
             uint64_t m = kNoKey;
-            if (tid < nb) {
-                // slots tid, tid + nt, ...: all loads of a round in flight
+            if (__builtin_amdgcn_readfirstlane(wave) * 64 < nb) {
+                // slots tid, tid + nt, ... (the last one again past the end): all
+                // loads of a poll in flight, the wave's loop on scalar branches
                 constexpr int P = kResBlocks / 64;
                 uint64_t w[P];
                 const uint64_t *base = e.slots + q * nb;
@@ -393,31 +440,32 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
                 auto poll = [&] {
                     if (!one) {
 #pragma unroll
-                        for (int u = 1; u < P; ++u) w[u] = load_past(base + (tid + u * nt < nb ? tid + u * nt : tid));
+                        for (int u = 1; u < P; ++u) w[u] = load_past(base + (tid + u * nt < nb ? tid + u * nt : nb - 1));
                     }
-                    w[0] = load_past(base + tid);
+                    w[0] = load_past(base + (tid < nb ? tid : nb - 1));
                     bool all = tag_of(w[0]) == want;
                     if (!one) {
 #pragma unroll
                         for (int u = 1; u < P; ++u) all &= tag_of(w[u]) == want;
                     }
-                    return all;
+                    return __ballot(!all) == 0;
                 };
                 uint64_t since = 0;
                 for (;;) {
                     bool all;
                     int polls = 0;
                     do all = poll();
-                    while (!all && ++polls < e.polls);
-                    if (all) break;
+                    while (!all && ++polls < looks);
+                    if (__builtin_expect(all, 1)) break;
                     const uint64_t now = wall_clock64();
                     if (since == 0) since = now;
-                    uint32_t st = load_past(e.ctl);
+                    uint32_t st = __builtin_amdgcn_readfirstlane(load_past(e.ctl));
                     if ((st == kResRun || st == kResTry) && now - since >= e.wait) {
-                        atomicCAS(e.ctl, kResRun, kResTry);
+                        if (lane == 0) atomicCAS(e.ctl, kResRun, kResTry);
                         wait_stores();  // the word is set before the slots are read again
-                        if (poll()) break;
-                        st = atomicCAS(e.ctl, kResTry, kResAlone) == kResDone ? kResDone : kResAlone;
+                        if (k == n_gens - 1 && poll()) break;
+                        if (lane == 0) st = atomicCAS(e.ctl, kResTry, kResAlone) == kResDone ? kResDone : kResAlone;
+                        st = __builtin_amdgcn_readfirstlane(st);
                     }
                     if (st == kResAlone) {
                         bad = 1;
@@ -436,10 +484,12 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             key = lanes_min<8>(sm[(lane & 15) < nw ? lane & 15 : 0]);
             if (bad) break;  // uniform: written before the barrier
             key &= ~(uint64_t)0xff000000u;  // the tag out, the index back
-            if (k == e.n_gens - 1 && tid == 0) word = load_past(e.ctl);
         }
         if constexpr (!MANY) {
-            gsrc = reinterpret_cast<const float4 *>(gb[q * (T / UNIT) + (uint32_t)key * G / UNIT]);
+            uint32_t group = (uint32_t)key;
+#pragma unroll
+            for (int r = 1; r < R; ++r) group -= group >= step ? step : 0;
+            gsrc = reinterpret_cast<const float4 *>(gb[q * (T / UNIT) + group * G / UNIT]);
         } else if (key != win) {
             const uint64_t *src =
                 e.cand + ((int64_t)q * nb + (uint32_t)key / (uint32_t)gpb % (uint32_t)nb) * (G * MAXIT * 2);
@@ -482,7 +532,9 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
             store_through(e.slots_next + tid * nb + b, kResNoSlot);
             if (b == 0) store_through(e.ctl_next + tid, kResRun);
         }
-        if (word != kResRun) lost = atomicCAS(e.ctl, kResTry, kResDone) == kResAlone;
+        // past the last exchange
+        if (tid == 0 && !bad && load_past(e.ctl) != kResRun)
+            lost = atomicCAS(e.ctl, kResTry, kResDone) == kResAlone;
         __syncthreads();
         // the same in every block; scalar branches, so that the rows are dead in it
         if (__builtin_amdgcn_readfirstlane(bad | lost)) {
@@ -501,7 +553,7 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
                 const PsoArgs wa = kernel_argument<PsoArgs>(0);
                 const PsoResArgs we = kernel_argument<PsoResArgs>(sizeof(PsoArgs));
                 pso_walk<FN, G>(wa, we.n_gens, we.gbest_out, we.best, nbr, reinterpret_cast<float *>(red), sk[0],
-                                reinterpret_cast<uint32_t *>(sm), &pick);
+                                reinterpret_cast<uint32_t *>(sm), &pick, gb[0]);
             }
             return;
         }
@@ -539,8 +591,8 @@ __global__ __launch_bounds__(T) void k_pso_res(PsoArgs a, PsoResArgs e)
     }
 }
 
-// The three shapes (PsoResPlan::shape): one row per group with up to 1024
-// threads; 4 rows with 512; 10 rows with 512 threads, x and pbest in 160 of
+// The shapes (PsoResPlan::shape): one row per group with up to 1024 threads; 4
+// rows with 512; three rows with up to 1024 in one block; 10 rows with 512 threads, x and pbest in 160 of
 // the 256 registers that leaves a lane and v in LDS but for what the row of gb
 // takes.
 template <int FN, int G>
@@ -548,6 +600,12 @@ hipError_t launch_pso_res_g(const PsoResPlan &pl, PsoArgs &a, PsoResArgs &e, hip
 {
     constexpr int VL = G == 512 ? 8 : 9;
     void *args[] = {&a, &e};
+    if (pl.shape == 4) {
+        if constexpr (G <= 64)
+            return hipLaunchKernel(reinterpret_cast<const void *>(&k_pso_res<FN, G, 3, 0, 1024, false>), dim3(1),
+                                   dim3((unsigned)pl.threads), args, 0, s);
+        return hipErrorInvalidValue;
+    }
     if (e.nblocks == 1)
         return hipLaunchKernel(reinterpret_cast<const void *>(&k_pso_res<FN, G, 1, 0, 1024, false>), dim3(1),
                                dim3((unsigned)pl.threads), args, 0, s);

@@ -6,7 +6,9 @@ generation.  Positions and velocities are compared bit for bit, personal-best
 fitness within the fitness tolerance, and the global-best index exactly
 (a tolerance tie would be reported as such).
 """
+import ctypes
 import math
+import os
 
 import numpy as np
 import pytest
@@ -292,7 +294,7 @@ STATE = ("x", "v", "pbest", "pfit", "fit", "gbest")
 # of several, and a function that looks at a neighbour across waves; the waits:
 # none, about an exchange (a call is given up anywhere in it, or not at all) and
 # the default
-GIVE_UP_CASES = [(2, 300, 10), (4, 1_999, 101), (1, 700, 500), (4, 520, 1_000), (3, 65, 2_100), (4, 40, 4_096),
+GIVE_UP_CASES = [(2, 1_000, 10), (4, 1_999, 101), (1, 700, 500), (4, 520, 1_000), (3, 65, 2_100), (4, 40, 4_096),
                  (5, 20_000, 13), (0, 4_500, 500), (4, 30_000, 70), (1, 2_100, 2_050)]
 
 
@@ -304,7 +306,7 @@ def test_resident_calls_given_up_are_done_by_one_block(evox_gpu, fn, N, D):
     kw = dict(seed=37, v_lo=-1.0, v_hi=1.0, **(dict(vmax=0.2 * (ub - lb), clamp_x=1) if N % 2 else {}))
     g, one = (evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, fn, N, D, lb, ub, **kw)) for _ in range(2))
     given_up = 0
-    for wait, n in ((0.0, 4), (0.0, 5), (1e-6, 6), (2e-6, 9), (3e-6, 5), (0.0, 4), (-1.0, 4)):
+    for wait, n in ((0.0, 4), (1e-8, 5), (1e-8, 7), (1e-6, 6), (2e-6, 9), (3e-6, 5), (0.0, 4), (-1.0, 4)):
         before = g.pso_wait(wait)
         g.step(n)
         for _ in range(n):
@@ -315,7 +317,7 @@ def test_resident_calls_given_up_are_done_by_one_block(evox_gpu, fn, N, D):
         after = g.pso_wait(-1.0)
         assert after - before in ((1,) if wait == 0.0 else (0, 1) if wait > 0.0 else (0,)), (wait, before, after)
         given_up += after - before
-    assert given_up >= 3
+    assert given_up >= 2
 
 
 def test_wait_argument(evox_gpu):
@@ -347,3 +349,61 @@ def test_resident_call_beside_a_long_kernel(evox_gpu):
     assert g.best() == one.best()
     print("calls done by one block:", g.pso_wait(-1.0), flush=True)
     assert long.t == 400_000 and math.isfinite(long.best()[0])
+
+
+# one block with two and three rows per lane group: from just above what it holds
+# with one (1024 lanes) to its most, for rows of 4 .. 64 lanes, and first sizes
+# beyond
+FEW_ROW_CASES = [(2, 257, 10), (4, 512, 16), (0, 513, 16), (1, 768, 16), (5, 769, 16), (4, 129, 60), (1, 256, 64),
+                 (2, 383, 57), (3, 65, 101), (5, 128, 128), (4, 192, 99), (4, 33, 250), (2, 64, 256), (0, 96, 200),
+                 (4, 17, 390), (1, 32, 512), (4, 33, 490), (3, 38, 505), (4, 40, 500), (0, 600, 3)]
+
+
+def small_pair(evox, ref, fn, N, D, stream=None):
+    lb, ub = {0: (-32.0, 32.0), 1: (-32.768, 32.768), 2: (-5.12, 5.12), 3: (-600.0, 600.0), 4: (-2.0, 2.0),
+              5: (-500.0, 500.0)}[fn]
+    kw = dict(v_lo=-1.0, v_hi=1.0, **(dict(vmax=0.2 * (ub - lb), clamp_x=1) if N % 2 else {}))
+    return (evox.Swarm(evox.make_params(evox.PSO, fn, N, D, lb, ub, seed=41, **kw), stream=stream),
+            ref.PSO(ref.make_params(fn, N, D, lb, ub, seed=41, **kw)))
+
+
+@pytest.mark.parametrize("fn,N,D", FEW_ROW_CASES)
+def test_short_calls_of_small_swarms(evox_gpu, ref, fn, N, D):
+    print(f"pso short fn={fn} N={N} D={D}", flush=True)
+    g, r = small_pair(evox_gpu, ref, fn, N, D)
+    for n in (1, 4, 30, 2):
+        g.step(n)
+        r.step(n)
+        compare_state(g, r, fn, f"after a call of {n}")
+        for name in ("x", "v", "pbest"):
+            assert not getattr(g, name)[:, D:].any(), f"{name} padding"
+
+
+def graph_nodes(graph):
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# the nodes of a graph of one generation and of six
+@pytest.mark.parametrize("N,D,one,six", [(100, 10, 1, 1), (300, 10, 1, 1), (768, 16, 1, 1), (769, 16, 3, 13),
+                                         (128, 128, 1, 1), (38, 490, 1, 1), (40, 490, 3, 13)])
+def test_captured_calls_of_small_swarms(evox_gpu, ref, N, D, one, six):
+    print(f"pso captured N={N} D={D}", flush=True)
+    for n, nodes in ((1, one), (6, six)):
+        st = torch.cuda.Stream()
+        g, r = small_pair(evox_gpu, ref, 2, N, D, stream=st)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=st):
+            g.step(n)
+        assert graph_nodes(graph) == nodes
+        for _ in range(3):
+            with torch.cuda.stream(st):
+                graph.replay()
+            r.t = 0
+            r.step(n)
+            torch.cuda.synchronize()
+            for name, want in (("x", r.x), ("v", r.v), ("pbest", r.p)):
+                assert np.array_equal(host(getattr(g, name), D), want), name
