@@ -178,8 +178,7 @@ __device__ __forceinline__ bool dominates_t(const float *a, const float *b)
 // clears are its later groups searched, so all the fronts together read each
 // of them about once.
 //
-// 32768 points, 3 objectives: coarse order 33 us and bits 121 (the vector ALU
-// half busy: the chip fills for little more than half of the pass), against 240
+// 32768 points, 3 objectives: coarse order 33 us and bits 81, against 240
 // for counting dominators over all pairs; fronts 12 us each, against 35 for
 // marking the points whose count is zero and subtracting their dominance.
 // ---------------------------------------------------------------------------
@@ -326,7 +325,8 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t acc, uint64_t mask)
 // a < b), so a strict pair is M - 1 vector compares and the add.
 // The positions' objectives are the same in every lane and come through scalar
 // loads, 64 bytes at a time: the strict pairs' from an array without the first
-// objective (from the padded one: a load per position, 145 us instead of 121).
+// objective (from the padded one a load per position: 145 us instead of 121 with four chunks
+// per block).
 template <int M, bool STRICT>
 __device__ __forceinline__ void chunk_bits(const float *__restrict__ fs, int64_t jc, const float (&fi)[M],
                                            uint32_t (&out)[8])
@@ -361,8 +361,13 @@ __device__ __forceinline__ void chunk_bits(const float *__restrict__ fs, int64_t
     }
 }
 
-// Block (ic, jg): the points of chunk ic against the four chunks of group jg.
-// The pointers are arguments of their own, marked unaliased, so that the
+// Block (ic, jc): the points of chunk ic against the positions of chunk jc; one
+// pair of chunks per block, since a block waits for the scalar loads of each
+// batch of positions in turn, and few blocks of several chunks leave it at that:
+// with four per block 2000 points of 8 objectives took 258 us in 16 blocks.  A
+// generation of 1000 x 30 with 8 objectives, four / one: 390 / 182 us (counting
+// over all pairs 324); 1000 x 100 with 3: 180 / 143; 16,384 x 100 with 3: 401 / 365;
+// 16,384 x 100 with 8: 1488 / 1228.  The pointers are arguments of their own, marked unaliased, so that the
 // positions' objectives (the same in every lane) come through scalar loads.
 template <int M>
 __global__ __launch_bounds__(kNsgaChunk) void k_nsga_bits(const float *__restrict__ fs,
@@ -370,30 +375,25 @@ __global__ __launch_bounds__(kNsgaChunk) void k_nsga_bits(const float *__restric
                                                           const float *__restrict__ range, int64_t n, int64_t chunks,
                                                           uint4 *__restrict__ W, uint32_t *__restrict__ ptr)
 {
-    const int64_t ic = blockIdx.x, pos = ic * kNsgaChunk + threadIdx.x;
+    const int64_t ic = blockIdx.x, jc = blockIdx.y, pos = ic * kNsgaChunk + threadIdx.x;
     constexpr int P = M <= 4 ? 4 : 8;
+    if (!chunk_open(range, ic, jc)) return;
     float fi[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) fi[m] = fs[pos * P + m];
-    uint32_t first = kNsgaNoWord;  // the first group of four words with a dominator
-    for (int64_t jc = 4 * (int64_t)blockIdx.y; jc < 4 * (int64_t)blockIdx.y + 4 && jc < chunks; ++jc) {
-        if (!chunk_open(range, ic, jc)) continue;
-        uint32_t w[8];
-        if (range[2 * jc + 1] < range[2 * ic])
-            chunk_bits<M, true>(fr, jc, fi, w);
-        else
-            chunk_bits<M, false>(fs, jc, fi, w);
-        if (pos >= n) continue;
-        W[w_index(chunks, ic, 2 * jc, threadIdx.x)] = make_uint4(w[0], w[1], w[2], w[3]);
-        W[w_index(chunks, ic, 2 * jc + 1, threadIdx.x)] = make_uint4(w[4], w[5], w[6], w[7]);
-        if (first == kNsgaNoWord) {
-            if (w[0] | w[1] | w[2] | w[3])
-                first = (uint32_t)(2 * jc);
-            else if (w[4] | w[5] | w[6] | w[7])
-                first = (uint32_t)(2 * jc + 1);
-        }
-    }
-    if (first != kNsgaNoWord) atomicMin(ptr + pos, first);
+    uint32_t w[8];
+    if (range[2 * jc + 1] < range[2 * ic])
+        chunk_bits<M, true>(fr, jc, fi, w);
+    else
+        chunk_bits<M, false>(fs, jc, fi, w);
+    if (pos >= n) return;
+    W[w_index(chunks, ic, 2 * jc, threadIdx.x)] = make_uint4(w[0], w[1], w[2], w[3]);
+    W[w_index(chunks, ic, 2 * jc + 1, threadIdx.x)] = make_uint4(w[4], w[5], w[6], w[7]);
+    // the first group of four words with a dominator
+    if (w[0] | w[1] | w[2] | w[3])
+        atomicMin(ptr + pos, (uint32_t)(2 * jc));
+    else if (w[4] | w[5] | w[6] | w[7])
+        atomicMin(ptr + pos, (uint32_t)(2 * jc + 1));
 }
 
 // Fronts are found kNsgaPeelBatch at a time without a host round trip:
@@ -734,7 +734,7 @@ hipError_t nsga_relate(const NsgaSortArgs &args, hipStream_t s)
     hipLaunchKernelGGL(k_nsga_place, dim3(blocks(n, 1024)), dim3(1024), 0, s, (int32_t)n, (const uint32_t *)a.hist,
                        (const uint32_t *)a.ptr, a.ord);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const dim3 chunks((unsigned)a.chunks), grid((unsigned)a.chunks, (unsigned)((a.chunks + 3) / 4));
+    const dim3 chunks((unsigned)a.chunks), grid((unsigned)a.chunks, (unsigned)a.chunks);
 #define EVOX_RELATE(MM)                                                                                        \
     hipLaunchKernelGGL((k_nsga_gather<MM>), chunks, dim3(kNsgaChunk), 0, s, a);                                \
     hipLaunchKernelGGL((k_nsga_bits<MM>), grid, dim3(kNsgaChunk), 0, s, (const float *)a.Fs,         \
