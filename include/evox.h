@@ -347,7 +347,9 @@ int evox_maes_step(evox_state *state, int64_t n_gens);
  *     together (parents first), then the survivors: whole fronts while
  *     they fit, and from the next front its members of largest crowding
  *     distance (lower index on ties), kept in their merged order.
- * Synchronizes the stream once per front sorted.  evox_best returns
+ * Synchronizes the stream once per front sorted.  evox_scratch_bytes counts a
+ * sort of 2N points: (2N)^2 / 8 bytes and a few per point and element (34 MB at
+ * N = 8192, 537 MB at the most, N = 32768).  evox_best returns
  * EVOX_EINVAL for this algorithm (there is no single best). */
 int evox_nsga2_step(evox_state *state, int64_t n_gens);
 
@@ -358,7 +360,9 @@ int evox_nsga2_step(evox_state *state, int64_t n_gens);
  * (per objective in order 0..M-1: +inf at either end of the front's order
  * of (value, index), else + (next - previous) / (last - first) when that
  * range is not zero).  1 <= n <= 65536, 2 <= M <= 8; scratch (device,
- * 256-byte aligned) of evox_nsga2_sort_scratch_bytes(n, M) bytes.  Returns
+ * 256-byte aligned) of evox_nsga2_sort_scratch_bytes(n, M) bytes, which grow
+ * with the square of n: n^2 / 8 for a bit per pair of points (2 MiB at 4096
+ * points, 134 MB at 32768, 537 MB at 65536) and up to 200 n.  Returns
  * when the result is in place (the stream is synchronized once per front). */
 size_t evox_nsga2_sort_scratch_bytes(int64_t n, int32_t M);
 int evox_nsga2_sort(const float *F, int64_t n, int32_t M, int32_t *front, double *crowd, void *scratch,

@@ -193,3 +193,64 @@ def test_population_returns_to_the_callers_buffer(evox_gpu, ref, gens):
         for name in ("x", "obj", "front", "crowd"):
             assert torch.equal(getattr(g, name), getattr(one, name)), name
         assert not g.x[:, 23:].any()
+
+
+def layers(n, M, count, seed):
+    """n points in `count` fronts known by construction: an antichain (multiples
+    of 2^-12 of one sum, so every value is exact) and its copies moved by k / 4
+    in every objective.  A step of dominance raises the sum, so it leads to a
+    later copy; the copies of one point are a chain.  The first objective's
+    ranges overlap.  Points past n are left out of the last front."""
+    rng = np.random.default_rng(seed)
+    m = (n + count - 1) // count
+    A = np.empty((m, M), np.float64)
+    A[:, :M - 1] = rng.integers(0, 4096 // (M - 1), size=(m, M - 1)) / 4096.0
+    A[:, M - 1] = 1.0 - A[:, :M - 1].sum(1)
+    F = np.concatenate([A + k / 4.0 for k in range(count)])[:n]
+    front = np.repeat(np.arange(count, dtype=np.int32), m)[:n]
+    order = rng.permutation(n)
+    return F[order].astype(np.float32), front[order]
+
+
+# the most points a sort takes, and one less
+@pytest.mark.parametrize("n,M,count", [(65536, 3, 16), (65535, 3, 61), (65536, 2, 9), (65535, 8, 4)])
+def test_sort_at_its_most_points(evox_gpu, ref, n, M, count):
+    print(f"nsga2 sort n={n} M={M} fronts={count}", flush=True)
+    F, want = layers(n, M, count, n + M)
+    front, crowd = gpu_sort(evox_gpu, F)
+    assert np.array_equal(front, want)
+    for k in sorted({0, 1, count - 1}):
+        members = np.nonzero(want == k)[0]
+        assert np.array_equal(crowd[members], ref.crowding(F[members], np.zeros(members.size, np.int32))), k
+
+
+def test_generation_of_the_largest_population(evox_gpu):
+    """N = 32768 (65536 merged points): the survivors hold every point that
+    precedes one of them, so sorted among themselves they have the fronts that
+    the merged sort gave them, and all but the last front their distances."""
+    N, D = 32768, 20
+    mk = lambda: evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.NSGA2, 0, N, D, 0.0, 1.0, seed=6, n_obj=3))  # noqa: E731
+    g, again = mk(), mk()
+    start = g.x.clone()
+    g.step(1)
+    again.step(1)
+    for name in ("x", "obj", "front", "crowd"):
+        assert torch.equal(getattr(g, name), getattr(again, name)), name
+    front, crowd = gpu_sort(evox_gpu, g.obj.cpu().numpy())
+    have = g.front.cpu().numpy()
+    assert np.array_equal(front, have)
+    whole = have < have.max()
+    assert whole.any() and np.array_equal(crowd[whole], g.crowd.cpu().numpy()[whole])
+    assert not g.x[:, D:].any() and not torch.equal(g.x, start)
+
+
+def test_scratch_grows_with_the_square_of_the_points(evox_gpu):
+    """n^2 / 8 bytes of dominator bits (chunks of 256 points) and a little
+    per point, as the header says."""
+    bytes_of = evox_gpu.lib().evox_nsga2_sort_scratch_bytes
+    for n in (1, 255, 4096, 65536):
+        bits = 2 * 16 * 256 * ((n + 255) // 256) ** 2
+        assert bits <= bytes_of(n, 3) <= bits + 200 * n + 40000
+    N = 32768
+    P = evox_gpu.make_params(evox_gpu.NSGA2, 0, N, 7, 0.0, 1.0, n_obj=3)
+    assert bytes_of(2 * N, 3) <= evox_gpu.evox_scratch_bytes(P) <= bytes_of(2 * N, 3) + 200 * N
