@@ -316,7 +316,8 @@ int evox_pgpe_step(evox_state *state, int64_t n_gens);
  *   - deviates z_kj from Philox(seed, (floor(j/4), k, t, 9)) (the Box-Muller
  *     layout of evox_fill_normal), steps d_k = M z_k (fp32 factors and
  *     sums on the matrix cores, each factor as three bf16 pieces; fp32 products
- *     where an element of M or s is outside 2^-80 .. 2^120 and not 0), samples fma(sigma, d_kj, y_j), fit = F(samples);
+ *     where an element is not 0 and outside 2^-80 .. 2^56 in M, 2^-40 .. 2^56
+ *     in s), samples fma(sigma, d_kj, y_j), fit = F(samples);
  *   - parents: the mu best in the argmin order;
  *   - y <- y + sigma sum w_i d_i, s <- (1 - c_s) s + sqrt(mu_eff c_s (2 - c_s))
  *     sum w_i z_i (fp64 sums, one rounding);

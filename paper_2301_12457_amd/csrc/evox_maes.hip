@@ -27,12 +27,14 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Six bf16 products cost 6 / 16 of one fp32 product on gfx950 (2.5 PFLOP/s
 // against 157 TFLOP/s).
 //
-// That holds for magnitudes whose pieces neither overflow nor fall below the
-// normal numbers: kSplitLo <= |x| < kSplitHi, or 0.  A block that meets another
-// element, of M or of the path s (a deviate is 0 or within 2^-40 .. 2^3), computes
-// its tile again with fp32 products (v_mfma_f32_16x16x4f32), so that infinities
-// and tiny numbers come out as they would without the split; a NaN stays one in
-// either product.
+// That holds for 0 and for magnitudes of 2^-80 .. 2^56 in M and 2^-40 .. 2^56 in
+// the path s (a deviate is 0 or within 2^-40 .. 2^3): the pieces are normal
+// numbers, no product of them falls more than 2^-18 below 2^-120, and no sum of
+// products overflows (2^56 2^56 of 2^15 columns), which the pieces of either sign
+// would turn into a NaN.  A block that meets another element computes its tile
+// again with fp32 products (v_mfma_f32_16x16x4f32), so that infinities and tiny
+// numbers come out as they would without the split; a NaN stays one in either
+// product.
 //
 // Z is split where it is drawn, into tiles of 3 pieces x 4 groups of 8 columns x
 // zr rows that a block copies to LDS as they are (16 lanes of one column group
@@ -61,7 +63,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // below D = 3, where one product's own rounding shows, the fp32 path is taken.
 // ---------------------------------------------------------------------------
 constexpr int kSpCols = 128;
-constexpr uint32_t kSplitLo = (127 - 80) << 23, kSplitHi = (127 + 120) << 23;  // 2^-80, 2^120
+constexpr uint32_t kSplitLo = (127 - 80) << 23, kPathLo = (127 - 40) << 23, kSplitHi = (127 + 56) << 23;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -85,11 +87,11 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &
     l = pack_bf16(a1 - __uint_as_float(m << 16), b1 - __uint_as_float(m & 0xffff0000u));
 }
 
-// Whether x cannot be split: not 0 and outside [2^-80, 2^120).
+// Whether an element of the path cannot be split: not 0 and outside [2^-40, 2^56).
 __device__ __forceinline__ bool odd_number(float x)
 {
     const uint32_t e = __float_as_uint(x) & 0x7fffffffu;
-    return e != 0 && (e < kSplitLo || e >= kSplitHi);
+    return e != 0 && (e < kPathLo || e >= kSplitHi);
 }
 
 // Deviates z_k (rows k < N, Philox stream 9 with the generation in the

@@ -378,3 +378,28 @@ def test_full_size_dense_matrix(evox_gpu, ref):
     M_gpu = g.mat[torch.from_numpy(rows).cuda()][:, :D].cpu().numpy().astype(np.float64)
     bad = np.argwhere(np.abs(M_gpu - M1) > Mb)
     assert bad.size == 0, f"matrix off at {bad[:5].tolist()}"
+
+
+@pytest.mark.parametrize("em, es", [(100, 40), (60, 70), (55, 75), (75, 75), (55, 90), (118, 10), (30, 110), (3, 119)])
+def test_path_product_beyond_the_range_of_its_factors(evox_gpu, ref, em, es):
+    """M s where an element of M is about 2^em and one of s about 2^es, each a
+    number that three bf16 pieces hold, and their sum of products overflows:
+    infinite as with fp32 products, never NaN from pieces of either sign."""
+    print(f"maes M 2^{em} s 2^{es}", flush=True)
+    N, D, i0 = 12, 70, 41
+    rng = np.random.default_rng(em + es)
+    g, r = pair(evox_gpu, ref, SPHERE, N, D, 3, -5.0, 5.0, 0.4)
+    r.M[:] = 0.0
+    r.M[i0] = (1.0 + rng.random(D)) * 2.0 ** em
+    r.s[:] = ((1.0 + rng.random(D)) * 2.0 ** es).astype(np.float32)
+    push(g, r)
+    g.step(1)
+    # row i0 of M: beta M + (c_1 / 2) (M s) s^T + finite terms, s still positive
+    assert np.all(g.v[:D].cpu().numpy() > 0)
+    row = g.mat[i0, :D].cpu().numpy()
+    assert np.all(row == math.inf), row[:4]
+
+
+@pytest.mark.parametrize("scale, where", [(51, "M"), (58, "M"), (57, "row"), (-78, "M"), (-42, "path"), (-37, "path")])
+def test_elements_around_the_split_range(evox_gpu, ref, scale, where):
+    test_elements_outside_the_split_range(evox_gpu, ref, scale, where)
