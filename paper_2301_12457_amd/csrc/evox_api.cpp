@@ -175,8 +175,14 @@ NsgaSortArgs nsga_sort_args(void *scratch, const NsgaSortScratch &l, const float
 // few output tiles, so the product is split along K until the blocks fill
 // the chip -- a whole number of rounds of resident blocks when the occupancy
 // is known (a partial last round idles most of the chip), else about 512
-// blocks -- with every slice at least 64 deep: with slices of 256 a problem of
-// 50 x 500 ran in 4 blocks (59 us per generation, 44 in 28 blocks).
+// blocks.  The slices are whole groups of three steps of 32 (the kernel runs a
+// group to its end): 50 x 2000 in 16 slices of 4 steps 55.1 us per generation, in
+// 11 of 6 52.1.  Below a least D that depends on the tile's rows, one block's work
+// per step, the launch that adds the slices up costs more than they gain (split /
+// not, per generation): 32 rows 16 x 200 42.8 / 39.9, 31 x 300 42.7 / 43.1, 16 x 400
+// 42.2 / 40.7, 31 x 400 42.0 / 44.1, 31 x 500 42.1 / 48.2; 64 rows 50 x 128 42.3 /
+// 39.8, 50 x 200 42.3 / 42.0, 63 x 200 43.2 / 44.8, 112 x 200 44.2 / 46.3; 112 rows
+// 100 x 128 44.4 / 46.2, 100 x 200 46.1 / 51.3.
 int mae_splits(int64_t N, int64_t D)
 {
     const int zr = mae_tile_rows(N + 1);
@@ -187,10 +193,10 @@ int mae_splits(int64_t N, int64_t D)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
         resident = (int64_t)cus * occupancy_mae_product(zr);
     int64_t sp = resident > 0 ? resident / tiles : (512 + tiles - 1) / tiles;
-    const int64_t deep = D / 64 > 1 ? D / 64 : 1;
-    if (sp > deep) sp = deep;
     if (sp > 16) sp = 16;
-    return (int)(sp < 1 ? 1 : sp);
+    if (sp < 1 || D < (zr == 32 ? 352 : zr == 64 ? 192 : 128)) sp = 1;
+    const int64_t steps = (D + 31) / 32, per = ((steps + sp - 1) / sp + 2) / 3 * 3;
+    return (int)((steps + per - 1) / per);
 }
 
 int make_plan(const evox_params *P, Plan *pl)

@@ -199,9 +199,6 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
     float big = 0.0f;
     uint32_t small = 0xffffffffu;
     bool sodd = false;  // an element of the path in this slice cannot be split
-    if (rows - i0 <= kSpRows)
-        for (int64_t k = 32 * (int64_t)s0 + tid; k < 32 * (int64_t)s1 && k < a.D; k += 256)
-            sodd = sodd || odd_number(a.s[k]);
     if (tid == 0) odd = a.D <= 2;
 
     if (s0 < s1) {
@@ -209,6 +206,10 @@ __global__ __launch_bounds__(256, 2) void k_mae_product(MaeArgs a, const float *
         load_a(s0);
 #pragma unroll
         for (int d = 0; d < kSpDepth; ++d) load_b(bq[d], s0 + d < last ? s0 + d : last);
+        // behind the first loads, not before them
+        if (rows - i0 <= kSpRows)
+            for (int64_t k = 32 * (int64_t)s0 + tid; k < 32 * (int64_t)s1 && k < a.D; k += 256)
+                sodd = sodd || odd_number(a.s[k]);
         store_a(0);
         load_a(s0 + 1 < last ? s0 + 1 : last);
         lds_barrier();
