@@ -391,10 +391,13 @@ hipError_t timed(evox_state *s, F &&launch, int64_t gens = 1)
     }
     auto &pr = s->ev[s->ev_used++];
     hipError_t e = hipEventRecord(pr.first, s->stream);
-    if (e != hipSuccess) return e;
-    e = launch();
-    if (e != hipSuccess) return e;
-    return hipEventRecord(pr.second, s->stream);
+    if (e == hipSuccess) e = launch();
+    if (e == hipSuccess) e = hipEventRecord(pr.second, s->stream);
+    if (e != hipSuccess) {  // not a launch to be counted: the caller may go on with another
+        --s->ev_used;
+        s->prof_gens -= gens;
+    }
+    return e;
 }
 
 hipError_t best_init(evox_state *s, float f, int64_t i) { return launch_best_init(s->best, f, i, s->stream); }
