@@ -471,7 +471,8 @@ int evox_copy(const float *src, float *dst, int64_t n, void *hip_stream);
  * nothing else.  For every i < N with winner_of[i] >= 0 (a loser; winner_of
  * device int32 [N], each winner index < N, every index the winner of at most
  * one loser and no loser a winner), in the generation kernel's traversal (row
- * groups of the CSO layout of D, losers in index order): the winner's row is
+ * groups of the CSO layout of D, ranges of as many individuals as that kernel
+ * takes for N, losers in index order): the winner's row is
  * gathered, the loser's x and v are read, and v_i = v_i + (x_w - x_i), x_i =
  * x_i + v_i are written (device x, v [N][ldx], 16-byte aligned, ldx % 4 == 0,
  * padding columns zero).  No random numbers, fitness or swarm mean.  With the

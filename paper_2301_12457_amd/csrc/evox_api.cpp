@@ -1448,7 +1448,8 @@ int evox_pair_move(float *x, float *v, int64_t N, int64_t D, int64_t ldx, const 
     if (!aligned16(x) || !aligned16(v)) return fail(EVOX_EALIGN, "x or v is not 16-byte aligned");
     Layout L;
     if (!row_layout(D, LAYOUT_CSO, &L)) return fail(EVOX_EINVAL, "no row layout for D = %lld", (long long)D);
-    hipError_t e = launch_pair_move(L.G, x, v, N, D, ldx, winner_of, (hipStream_t)hip_stream);
+    hipError_t e = launch_pair_move(L.G, x, v, N, D, ldx, winner_of, cso_sweep(N, block_for(L.G) / L.G),
+                                    (hipStream_t)hip_stream);
     if (e != hipSuccess) return hip_fail(e, "pair move");
     return EVOX_OK;
 }

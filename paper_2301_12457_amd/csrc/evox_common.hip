@@ -573,7 +573,7 @@ hipError_t launch_perm(const PermArgs &a, hipStream_t s)
 
 // ---------------------------------------------------------------------------
 // Diagnostic: the data movement of one swarm-mean CSO generation alone, in
-// the generation kernel's traversal (ranges of kCsoSweep individuals, the
+// the generation kernel's traversal (ranges of `sweep` individuals, the
 // losers listed in index order, one row group per listed loser): gather the
 // winner's row, read the loser's x and v, write v + (x_w - x) and the moved
 // x.  No random numbers, no fitness, no column sums: the floor the
@@ -581,11 +581,12 @@ hipError_t launch_perm(const PermArgs &a, hipStream_t s)
 // ---------------------------------------------------------------------------
 template <int G>
 __global__ __launch_bounds__(block_for(G)) void k_pair_move(float *x, float *v, int64_t N, int64_t D, int64_t ldx,
-                                                            const int32_t *winner_of)
+                                                            const int32_t *winner_of, int32_t sweep)
 {
-    constexpr int B = block_for(G), RPB = B / G, NW = B / 64, R = kCsoSweep;
-    static_assert(R <= B, "one individual per thread in the listing phase");
-    __shared__ int32_t lst_l[R], lst_w[R];
+    constexpr int B = block_for(G), RPB = B / G, NW = B / 64;
+    static_assert(kCsoSweep <= B, "one individual per thread in the listing phase");
+    __shared__ int32_t lst_l[kCsoSweep], lst_w[kCsoSweep];
+    const int R = sweep;
     __shared__ int32_t wcnt[NW];
     const int tid = threadIdx.x, g = tid % G, slot = tid / G, lane = tid & 63, wave = tid >> 6;
     const int64_t C4 = (D + 3) >> 2;
@@ -627,33 +628,34 @@ __global__ __launch_bounds__(block_for(G)) void k_pair_move(float *x, float *v, 
 
 template <int G>
 static hipError_t launch_pair_move_g(float *x, float *v, int64_t N, int64_t D, int64_t ldx, const int32_t *winner_of,
-                                     hipStream_t s)
+                                     int32_t sweep, hipStream_t s)
 {
     int occ = 0, dev = 0, cus = 0;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_pair_move<G>, block_for(G), 0);
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
                                                  hipSuccess)
         cus = 256;
-    int64_t grid = (N + kCsoSweep - 1) / kCsoSweep;
+    int64_t grid = (N + sweep - 1) / sweep;
     const int64_t resident = (int64_t)cus * (occ > 0 ? occ : 1);
     if (grid > resident) grid = resident;
-    hipLaunchKernelGGL((k_pair_move<G>), dim3((unsigned)grid), dim3(block_for(G)), 0, s, x, v, N, D, ldx, winner_of);
+    hipLaunchKernelGGL((k_pair_move<G>), dim3((unsigned)grid), dim3(block_for(G)), 0, s, x, v, N, D, ldx, winner_of,
+                       sweep);
     return hipGetLastError();
 }
 
 hipError_t launch_pair_move(int G, float *x, float *v, int64_t N, int64_t D, int64_t ldx, const int32_t *winner_of,
-                            hipStream_t s)
+                            int32_t sweep, hipStream_t s)
 {
     switch (G) {
-        case 4: return launch_pair_move_g<4>(x, v, N, D, ldx, winner_of, s);
-        case 8: return launch_pair_move_g<8>(x, v, N, D, ldx, winner_of, s);
-        case 16: return launch_pair_move_g<16>(x, v, N, D, ldx, winner_of, s);
-        case 32: return launch_pair_move_g<32>(x, v, N, D, ldx, winner_of, s);
-        case 64: return launch_pair_move_g<64>(x, v, N, D, ldx, winner_of, s);
-        case 128: return launch_pair_move_g<128>(x, v, N, D, ldx, winner_of, s);
-        case 256: return launch_pair_move_g<256>(x, v, N, D, ldx, winner_of, s);
-        case 512: return launch_pair_move_g<512>(x, v, N, D, ldx, winner_of, s);
-        case 1024: return launch_pair_move_g<1024>(x, v, N, D, ldx, winner_of, s);
+        case 4: return launch_pair_move_g<4>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 8: return launch_pair_move_g<8>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 16: return launch_pair_move_g<16>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 32: return launch_pair_move_g<32>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 64: return launch_pair_move_g<64>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 128: return launch_pair_move_g<128>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 256: return launch_pair_move_g<256>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 512: return launch_pair_move_g<512>(x, v, N, D, ldx, winner_of, sweep, s);
+        case 1024: return launch_pair_move_g<1024>(x, v, N, D, ldx, winner_of, sweep, s);
         default: return hipErrorInvalidValue;
     }
 }

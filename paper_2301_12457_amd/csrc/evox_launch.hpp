@@ -321,9 +321,10 @@ hipError_t launch_stream_copy(const float *src, float *dst, int64_t n, hipStream
 // n % 4 == 0.
 hipError_t launch_pso_stream(float *x, float *v, const float *p, int64_t n, hipStream_t s);
 // The data movement of a swarm-mean CSO generation with G lanes per row
-// (diagnostic): loser i = every index with winner_of[i] >= 0.
+// (diagnostic), in ranges of `sweep` individuals (1 .. kCsoSweep): loser i = every
+// index with winner_of[i] >= 0.
 hipError_t launch_pair_move(int G, float *x, float *v, int64_t N, int64_t D, int64_t ldx, const int32_t *winner_of,
-                            hipStream_t s);
+                            int32_t sweep, hipStream_t s);
 // dst[0 .. ldx) = src[0 .. ldx).
 hipError_t launch_copy_row(const float *src, float *dst, int64_t ldx, hipStream_t s);
 hipError_t launch_fill(float *dst, int64_t n, float value, hipStream_t s);

@@ -231,3 +231,25 @@ def test_range_lengths_match_oracle(evox_gpu, ref, fn, N, D, local):
         else:
             cso_lockstep(ref, g, r, f"generation {t}")
         compare(g, r, fn, f"generation {t}")
+
+
+# the diagnostic's ranges follow the generation kernel's: short ones for few
+# individuals, 128 for many, an end inside a range
+@pytest.mark.parametrize("N,D", [(2, 5), (1_001, 1_000), (5_121, 100), (90_001, 10), (131, 4_100)])
+def test_pair_move_moves_every_loser_once(evox_gpu, N, D):
+    ldx = evox_gpu.pitch(D, evox_gpu.CSO)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.zeros((N, ldx), device="cuda")
+    x[:, :D] = torch.rand((N, D), device="cuda", generator=gen)
+    v = torch.zeros_like(x)
+    v[:, :D] = torch.rand((N, D), device="cuda", generator=gen)
+    perm = torch.randperm(N, device="cuda", generator=gen)
+    pairs = N // 2
+    losers, winners = perm[1:2 * pairs:2], perm[0:2 * pairs:2]
+    winner_of = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    winner_of[losers] = winners.int()
+    want_v, want_x = v.clone(), x.clone()
+    want_v[losers] = v[losers] + (x[winners] - x[losers])
+    want_x[losers] = x[losers] + want_v[losers]
+    evox_gpu.evox_pair_move(x, v, N, D, ldx, winner_of)
+    assert torch.equal(x, want_x) and torch.equal(v, want_v)
