@@ -937,7 +937,9 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
     // n - 1 between the first evaluation and the last move of another's
     const bool small = pl.L.G <= 64 && s->P.N * s->P.D <= 16384;
     const bool graph = pl.res.nblocks != 1 && capturing(s->stream);
-    const bool many = pl.res.nblocks > 1 && s->res_calls >= 0 && s->res_rest == 0 && !graph;
+    const bool rest = s->res_rest > 0;
+    if (rest) --s->res_rest;
+    const bool many = pl.res.nblocks > 1 && s->res_calls >= 0 && !rest && !graph;
     const bool one = pl.res_one.nblocks == 1 && !(many && n_gens > pl.res_one_gens);
     if (pl.res.nblocks == 1 || one || (many && n_gens >= kResMinGens)) {
         // the swarm on the chip for the whole call, one launch (a launch of
@@ -962,7 +964,6 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
         (void)hipGetLastError();  // the device does not take the launch: the grid-wide kernels from now on
         s->res_calls = -1;
     }
-    if (s->res_rest > 0) --s->res_rest;
     // generation t: evaluate x_t, personal and global bests
     const auto first = [&] { return launch_pso(fn, pl.L, PSO_EVAL, a, s->stream); };
     const auto last = [&] { return launch_pso(fn, pl.L, PSO_MOVE, a, s->stream); };
