@@ -501,7 +501,7 @@ int evox_philox_fill(uint64_t seed, uint32_t c1, uint32_t c2, uint32_t c3, int64
  * evox_profile_read waits for the stream and returns the summed duration of
  * the timed generation-kernel launches, the number of generations those
  * launches performed (one per fused launch; a PSO call that runs in one launch
- * counts its n generations for N D <= 16384, else n - 1, as the fused launches
+ * counts its n generations for N D <= 16384 or in one block, else n - 1, as the fused launches
  * between the first evaluation and the last move would), and the number of
  * rows whose personal best improved in every evaluation since profiling
  * started (PSO). */

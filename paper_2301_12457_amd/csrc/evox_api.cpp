@@ -933,8 +933,9 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
     const int fn = s->P.fn_id;
     PsoArgs a = pso_args(s);
     hipError_t e;
-    // what evox_profile counts: all n generations of a small swarm's call, the
-    // n - 1 between the first evaluation and the last move of another's
+    // what evox_profile counts: all n generations of a small swarm's call or of
+    // one block's, the n - 1 between the first evaluation and the last move of
+    // another's
     const bool small = pl.L.G <= 64 && s->P.N * s->P.D <= 16384;
     const bool graph = pl.res.nblocks != 1 && capturing(s->stream);
     const bool rest = s->res_rest > 0;
@@ -954,7 +955,7 @@ int evox_pso_step(evox_state *s, int64_t n_gens)
                             wait < 1e-3 ? 1 : 32, at<uint64_t>(s->B.scratch, pl.res_cand), s->B.gbest, s->best};
         a.t = (uint32_t)s->t;
         e = timed(s, [&] { return launch_pso_res(fn, pl.L.G, res, a, ra, s->stream); },
-                  small ? n_gens : n_gens - 1);
+                  small || one ? n_gens : n_gens - 1);
         if (e == hipSuccess) {
             if (nb > 1) s->res_calls ^= 1;
             s->t += n_gens;

@@ -407,3 +407,16 @@ def test_captured_calls_of_small_swarms(evox_gpu, ref, N, D, one, six):
             torch.cuda.synchronize()
             for name, want in (("x", r.x), ("v", r.v), ("pbest", r.p)):
                 assert np.array_equal(host(getattr(g, name), D), want), name
+
+
+# one generation a call: in one block above and below 16384 elements, and grid-wide
+@pytest.mark.parametrize("N,D,gens", [(300, 10, 3), (300, 64, 3), (2_000, 100, 0)])
+def test_profile_counts_the_generations_of_short_calls(evox_gpu, N, D, gens):
+    g = evox_gpu.Swarm(evox_gpu.make_params(evox_gpu.PSO, 2, N, D, -5.12, 5.12, seed=1))
+    g.step(1)
+    g.profile(True)
+    for _ in range(3):
+        g.step(1)
+    ms, launches, improved = g.profile_read()
+    g.profile(False)
+    assert launches == gens and (ms > 0) == (gens > 0) and 0 < improved <= 3 * N
