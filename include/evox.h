@@ -501,10 +501,10 @@ int evox_philox_fill(uint64_t seed, uint32_t c1, uint32_t c2, uint32_t c3, int64
  * evox_profile_read waits for the stream and returns the summed duration of
  * the timed generation-kernel launches, the number of generations those
  * launches performed (one per fused launch; a PSO call that runs in one launch
- * counts its n generations for N D <= 16384 or in one block, else n - 1, as the fused launches
- * between the first evaluation and the last move would), and the number of
- * rows whose personal best improved in every evaluation since profiling
- * started (PSO). */
+ * counts its n generations for N D <= 16384 or in one block, else n - 1, as
+ * the fused launches between the first evaluation and the last move would),
+ * and the number of rows whose personal best improved in every evaluation
+ * since profiling started (PSO). */
 int evox_profile(evox_state *state, int enable);
 int evox_profile_read(evox_state *state, double *fused_ms, int64_t *fused_launches,
                       int64_t *improved_rows);
